@@ -16,8 +16,8 @@
 // x_i and f^eq_i are recomputed from per-axis factors wherever they are
 // needed instead of being kept (Q doubles each).  The common case -- alpha_* =
 // 2 and max_i |x_i| small -- is one unrolled pass with a short series.  Rare
-// cases (a longer series, the log1p forms, the root solvers) run as
-// non-unrolled loops over the directions so they add little register
+// cases (a longer series, the log1p forms) run as passes of their own
+// (sweep()), a few directions at a time, so that they add little register
 // pressure to the common path.
 #pragma once
 
@@ -93,11 +93,6 @@ template <class R>
 __device__ __forceinline__ R sel3(const R (&a)[3], int d) {
   return d == 0 ? a[0] : (d == 1 ? a[1] : a[2]);
 }
-template <class R>
-__device__ __forceinline__ R sel9(const R (&a)[3][3], int dx, int dy) {
-  return sel3(a[0], dy) * R(dx == 0) + sel3(a[1], dy) * R(dx == 1) + sel3(a[2], dy) * R(dx == 2);
-}
-
 // Series lengths of the three tiers and their validity bounds on
 // max_i |x_i|: truncating E and O after K terms changes alpha by about
 // 2 x^(2K+1)/((2K+3)(2K+2)), kept below 2^-53 (FP64) or 2^-24 (FP32).
@@ -269,11 +264,11 @@ struct Site {
   R f01[3][3]; // rho e[0][dx] e[1][dy]:  f^eq_i = f01[dx][dy] e2[dz]
   R r01[3][3]; // ie[0][dx] ie[1][dy] / rho: 1/f^eq_i = r01[dx][dy] ie2[dz]
   R e2[3], ie2[3];  // e[2][dz], ie[2][dz]
-  // where the populations came from, for the loops of the rare paths
+  // where the populations came from, for the rare tier's passes with 27
+  // directions
   const T* src;
   uint32_t site;
   const SimDesc* desc;
-  Where w;  // filled by locate_rare() before a rare-path loop
 
   // -- unrolled accessors (compile-time i) --------------------------------
   // The stored value is widened in each pass (cvt_fresh) rather than Q
@@ -360,21 +355,48 @@ struct Site {
     return h;
   }
 
-  // -- loop accessors (run-time, wavefront-uniform i) -----------------------
-  // Register arrays are never indexed at run time (that would move them to
-  // scratch memory); the population is re-read from the source buffer,
-  // whose lines this wavefront has just brought into the caches.
-  __device__ __forceinline__ void xfe(int i, R& xi, R& fi, R* gout = nullptr) const {
-    const int dx = i % 3, dy = D > 1 ? (i / 3) % 3 : 0, dz = D > 2 ? i / 9 : 0;
-    const int nz0 = (dx == 0) + (D > 1 && dy == 0) + (D > 2 && dz == 0);
-    const R W = R(nz0 == 0 ? 1.0 : nz0 == 1 ? 4.0 : nz0 == 2 ? 16.0 : 64.0) / R(L::den());
-    const uint32_t sp = sel3(w.zs, dz) + sel3(w.ys, dy) + sel3(w.xs, dx);
-    const T gv = *(const gptr<T>)((gaddr)(uintptr_t)src + pidx<Q>(sp, i) * sizeof(T));
-    const R gi = Codec<S, R>::dec(gv, W, rho_ref);
-    fi = sel9(f01, dx, dy) * sel3(e2, dz);
-    const R ri = sel9(r01, dx, dy) * sel3(ie2, dz);
-    xi = fma(gi, ri, R(-1));
-    if (gout) *gout = gi;
+  // One pass f(i, 1/W_i, x_i, f^eq_i, g_i) over the directions for the rare
+  // tier, the root solvers' log1p passes and the collision that follows
+  // them.  Up to nine directions: on the registers' populations, three
+  // directions at a time (the fences bound what the scheduler interleaves,
+  // and with it the registers held; three independent logarithm chains hide
+  // most of each other's latency).  With 27 directions the populations are
+  // not kept through the logarithms (registers): a loop over the rows
+  // (c_y, c_z) re-reads the three of each, together, from the caches this
+  // wavefront has just filled.
+  template <class F>
+  __device__ __forceinline__ void sweep(const F& f) const {
+    if constexpr (D == 3) {
+      const Where w = locate<D>(*desc, site);
+#pragma unroll 1
+      for (int n = 0; n < 9; ++n) {  // n = dy + 3 dz
+        const int dy = n % 3, dz = n / 3, z = (dy == 0) + (dz == 0);
+        const uint32_t ro = sel3(w.zs, dz) + sel3(w.ys, dy);
+        T gv[3];
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+          gv[dx] = *(const gptr<T>)((gaddr)(uintptr_t)src +
+                                    pidx<Q>(ro + w.xs[dx], dx + 3 * n) * sizeof(T));
+        const R ez = sel3(e2, dz), iz = sel3(ie2, dz);
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) {
+          // W of c_x with z zeros among c_y, c_z (the direction with those digits)
+          const int i0 = dx, i1 = dx + 3, i2 = dx + 12;
+          const R W = z == 2 ? R(L::W(i0)) : z == 1 ? R(L::W(i1)) : R(L::W(i2));
+          const R iW = z == 2 ? R(L::invW(i0)) : z == 1 ? R(L::invW(i1)) : R(L::invW(i2));
+          const R gi = Codec<S, R>::dec(gv[dx], W, rho_ref);
+          f(dx + 3 * n, iW, fma(gi, sel3(r01[dx], dy) * iz, R(-1)), sel3(f01[dx], dy) * ez, gi);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    } else {
+      const Pass p = pass_opaque();
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        f(i, R(L::invW(i)), x(i, p), fe(i, p), g(i));
+        if (i % 3 == 2) __builtin_amdgcn_sched_barrier(0);
+      }
+    }
   }
 };
 
@@ -453,7 +475,6 @@ struct SiteDevT {
   const T* src;
   uint32_t site;
   const SimDesc* desc;
-  Where w;  // filled by locate() before a rare-path loop
 
   // s_i from the kept value (FP32 storage holds f_i: one rounding)
   __device__ __forceinline__ A s(int i) const {
@@ -575,39 +596,69 @@ struct SiteDevT {
     return h;
   }
 
-  // -- loop accessors (run-time, wavefront-uniform i) -----------------------
-  // The population is re-read from the source buffer (see Site::xfe).
-  // W_i = num / den with num = 4^(number of zero components of c_i); both
-  // quotients round as float(L::W(i)) and float(L::invW(i)) do (den / num is
-  // exact)
-  __device__ __forceinline__ static float weight_num(int i) {
-    const int dx = i % 3, dy = D > 1 ? (i / 3) % 3 : 0, dz = D > 2 ? i / 9 : 0;
-    const int nz0 = (dx == 0) + (D > 1 && dy == 0) + (D > 2 && dz == 0);
-    return nz0 == 0 ? 1.0f : nz0 == 1 ? 4.0f : nz0 == 2 ? 16.0f : 64.0f;
+  // One pass f(i, s_i, s^eq_i, W_i) over the directions for the rare tier and
+  // the collision that follows it (see Site::sweep), and the values x_i and
+  // f^eq_i of a direction as the rare tier forms them: through the reciprocal
+  // of rho_ref + s^eq_i itself, not the per-axis factors.
+  template <class F>
+  __device__ __forceinline__ void sweep_dev(const F& f) const {
+    if constexpr (D == 2 && sizeof(T) == 2) {
+      // one direction at a time: with more in flight this kernel loses the
+      // six waves per SIMD that its common path runs at (78 VGPRs), 4 % of
+      // its time at 4096^2
+      const Where w = locate<D>(*desc, site);
+#pragma unroll 1
+      for (int i = 0; i < Q; ++i) {
+        const int dx = i % 3, dy = i / 3, z = (dx == 0) + (dy == 0);
+        const T gv = *(const gptr<T>)((gaddr)(uintptr_t)src +
+                                      pidx<Q>(sel3(w.ys, dy) + sel3(w.xs, dx), i) * sizeof(T));
+        const A q0 = sel3(seqA[0], dy), q1 = sel3(seqA[1], dy), q2 = sel3(seqA[2], dy);
+        f(i, A(gv), dx == 0 ? q0 : (dx == 1 ? q1 : q2),
+          z == 2 ? L::W(0) : z == 1 ? L::W(1) : L::W(4));
+      }
+    } else if constexpr (D == 3) {
+      const Where w = locate<D>(*desc, site);
+#pragma unroll 1
+      for (int n = 0; n < 9; ++n) {  // n = dy + 3 dz
+        const int dy = n % 3, dz = n / 3, z = (dy == 0) + (dz == 0);
+        const uint32_t ro = sel3(w.zs, dz) + sel3(w.ys, dy);
+        T gv[3];
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+          gv[dx] = *(const gptr<T>)((gaddr)(uintptr_t)src +
+                                    pidx<Q>(ro + w.xs[dx], dx + 3 * n) * sizeof(T));
+        const A dl = sel3(dlz, dz);
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) {
+          const int i0 = dx, i1 = dx + 3, i2 = dx + 12;  // as in Site::sweep
+          const A iW = z == 2 ? A(L::invW(i0)) : z == 1 ? A(L::invW(i1)) : A(L::invW(i2));
+          A si = A(gv[dx]);
+        if constexpr (!S::dev) si = fma(si, iW, -r);
+          f(dx + 3 * n, si, fma(sel3(seqB[dx], dy), dl, sel3(seqA[dx], dy)),
+            z == 2 ? L::W(i0) : z == 1 ? L::W(i1) : L::W(i2));
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    } else {
+      const Pass p = pass_opaque();
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        f(i, s(i), seq(i, p), L::W(i));
+        if (i % 3 == 2) __builtin_amdgcn_sched_barrier(0);
+      }
+    }
   }
-  __device__ __forceinline__ static float weight_of(int i) { return weight_num(i) / float(L::den()); }
-  // w_lo of the weight weight_of(i) rounds (the four weights of the lattice)
-  __device__ __forceinline__ static float weight_lo(int i) {
-    const float n = weight_num(i);
-    return n == 1.0f ? w_lo(1.0 / L::den()) : n == 4.0f ? w_lo(4.0 / L::den())
-         : n == 16.0f ? w_lo(16.0 / L::den()) : w_lo(64.0 / L::den());
+  __device__ __forceinline__ double x_far(A si, A seqi) const {
+    return double((si - seqi) * rcp_hw(r + seqi));
   }
-  __device__ __forceinline__ static float invweight_of(int i) { return float(L::den()) / weight_num(i); }
-  __device__ __forceinline__ void sq(int i, float& si, float& seqi) const {
-    const int dx = i % 3, dy = D > 1 ? (i / 3) % 3 : 0, dz = D > 2 ? i / 9 : 0;
-    const uint32_t sp = sel3(w.zs, dz) + sel3(w.ys, dy) + sel3(w.xs, dx);
-    const T gv = *(const gptr<T>)((gaddr)(uintptr_t)src + pidx<Q>(sp, i) * sizeof(T));
-    if constexpr (S::dev) si = float(gv);
-    else si = fmaf(float(gv), invweight_of(i), -r);
-    // the selections multiply by 0 and 1 and add zeros: exact
-    const float sa = sel9(seqA, dx, dy);
-    seqi = D > 2 ? fmaf(sel9(seqB, dx, dy), sel3(dlz, dz), sa) : sa;
+  __device__ __forceinline__ double fe_far(A seqi, double W) const {
+    return double(A(W) * (r + seqi));
   }
-  __device__ __forceinline__ void xfe(int i, double& xi, double& fi, double* = nullptr) const {
-    float si, seqi;
-    sq(i, si, seqi);
-    xi = double((si - seqi) * __builtin_amdgcn_rcpf(r + seqi));
-    fi = double(weight_of(i) * (r + seqi));
+  template <class F>
+  __device__ __forceinline__ void sweep(const F& f) const {
+    sweep_dev([&](int i, A si, A seqi, double W) {
+      f(i, 0.0, x_far(si, seqi), fe_far(seqi, W), 0.0);
+    });
   }
 };
 template <int D, class S>
@@ -617,12 +668,7 @@ using SiteDev = SiteDevT<D, S, float>;
 template <class V, class R>
 __device__ __forceinline__ R S_log(const V& v, R a) {
   R s = R(0);
-#pragma unroll 1
-  for (int i = 0; i < V::Q; ++i) {
-    R xi, fi;
-    v.xfe(i, xi, fi);
-    s += fi * phi_log<R>((R(1) - a) * xi);
-  }
+  v.sweep([&](int, R, R xi, R fi, R) { s += fi * phi_log<R>((R(1) - a) * xi); });
   return s;
 }
 
@@ -633,16 +679,13 @@ __device__ __forceinline__ void S_dS_log(const V& v, R a, R& Sv, R& dS, R* sA = 
   Sv = R(0);
   dS = R(0);
   R sa = R(0);
-#pragma unroll 1
-  for (int i = 0; i < V::Q; ++i) {
-    R xi, fi;
-    v.xfe(i, xi, fi);
+  v.sweep([&](int, R, R xi, R fi, R) {
     const R y = (R(1) - a) * xi;
     const R l = dlog_clamped<R>(y);
     Sv += fi * ((y <= R(-1)) ? R(1) : (R(1) + y) * l - y);
     dS -= fi * xi * l;
     sa = fma(fi, fabs(xi), sa);
-  }
+  });
   if (sA) *sA = sa;
 }
 
@@ -753,10 +796,9 @@ __device__ __forceinline__ void S_dS_series(const V& v, R a, R& Sv, R& dS, R& sA
 
 // S(a), S'(a) for one Newton iteration: the unrolled register passes when
 // every active lane's |(1 - a) x_i| fits a series tier (xabs = max_i |x_i|
-// of the lane), else the rolled pass with the library logarithm.
+// of the lane), else the pass with the library logarithm.
 template <class V, class R>
-__device__ __forceinline__ void S_dS_newton(V& v, const SimDesc& d, R a, R xabs, R& Sv, R& dS,
-                                            R& sA) {
+__device__ __forceinline__ void S_dS_newton(const V& v, R a, R xabs, R& Sv, R& dS, R& sA) {
   if constexpr (std::is_same<R, double>::value) {
     const R yb = fabs(R(1) - a) * xabs;
     if (__all(yb <= R(Log1pM::ymax))) {
@@ -768,9 +810,6 @@ __device__ __forceinline__ void S_dS_newton(V& v, const SimDesc& d, R a, R xabs,
       return;
     }
   }
-  // the rolled pass re-reads the populations: their source offsets are
-  // formed here, not kept live through the register passes
-  v.w = locate<V::kDim>(d, v.site);
   S_dS_log(v, a, Sv, dS, &sA);
 }
 
@@ -779,16 +818,10 @@ __device__ __forceinline__ void S_dS_newton(V& v, const SimDesc& d, R a, R xabs,
 template <class V, class R>
 __device__ __forceinline__ void rare_sums(const V& v, R astar, bool star2, R xabs, R& Dv, R& Ds,
                           R& Gs) {
-  constexpr int Q = V::Q;
   if (star2 && xabs <= Base<R>::thrL) {
     R sE = R(0), sO = R(0);
     const SeriesK<R, Base<R>::KL> ser;
-#pragma unroll 1
-    for (int i = 0; i < Q; ++i) {
-      R xi, fi;
-      v.xfe(i, xi, fi);
-      ser.accum(xi, fi, sE, sO);
-    }
+    v.sweep([&](int, R, R xi, R fi, R) { ser.accum(xi, fi, sE, sO); });
     R cE, cO;
     series_scale<R, Base<R>::KL>(cE, cO);
     sE *= cE;
@@ -799,16 +832,13 @@ __device__ __forceinline__ void rare_sums(const V& v, R astar, bool star2, R xab
     return;
   }
   R sD = R(0), sS = R(0), sG = R(0);
-#pragma unroll 1
-  for (int i = 0; i < Q; ++i) {
-    R xi, fi;
-    v.xfe(i, xi, fi);
+  v.sweep([&](int, R, R xi, R fi, R) {
     const R px = phi_log<R>(xi);
     const R py = phi_log<R>((R(1) - astar) * xi);
     sD += fi * px;
     sS += fi * py;
     sG += fi * (py - px);
-  }
+  });
   Dv = sD;
   Ds = sS;
   Gs = sG;
@@ -834,7 +864,6 @@ enum { kPhaseAll = 0, kPhaseCommon = 1, kPhaseRare = 2 };
 template <int MODE, int PHASE, class V>
 __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const SimDesc& d) {
   using R = typename V::Real;
-  constexpr int D = V::kDim;
   constexpr int Q = V::Q;
   AlphaOut<R> o;
   o.deferred = false;
@@ -879,9 +908,6 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
     }
     return o;
   }
-  // The rolled passes (rare tier, root solvers) re-read the populations
-  // from the source buffer; their source offsets (v.w) are formed just
-  // before each such pass rather than kept live through the whole update.
   // Common tier: x_i, max|x_i| and the KC-term series sums in one pass.
   // With 2-byte storage the stored result carries 11 bits: for the closed
   // form one term (E = sum f^eq x^2 / 2, O = sum f^eq x^3 / 6) up to
@@ -939,21 +965,18 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
       sO *= cO;
     }
   } else {
-    // only deferred lanes are active: max|x_i| again, by the loop accessors
-    v.w = locate<D>(d, v.site);
-#pragma unroll 1
-    for (int i = 0; i < Q; ++i) {
-      R xi, fi;
-      v.xfe(i, xi, fi);
+    // only deferred lanes are active: max|x_i| again, and max x_i
+    v.sweep([&](int, R, R xi, R, R) {
       xabs = fmax(xabs, fabs(xi));
-    }
+      xmax = fmax(xmax, xi);
+    });
   }
   // D = H(f) - H(f^eq), Gs = H(f*(a_*)) - H(f), Ds = H(f*(a_*)) - H(f^eq); at
   // alpha_* = 2: D = E - O, Ds = E + O, Gs = 2 O.
   R Dv = sE - sO, Ds = sE + sO, Gs = R(2) * sO;
   // max|x| <= thrM < 1 implies max x <= 1, i.e. alpha_* = 2.  A lane in the
   // rare phase was deferred by the common phase and stays rare: max|x_i|
-  // formed again by the loop accessors may round differently and must not
+  // formed again by another sequence may round differently and must not
   // send it back to a tier whose sums it has not formed.
   const bool common = PHASE != kPhaseRare && xabs <= thrC;
   const bool mid = PHASE != kPhaseRare && !common && xabs <= Base<R>::thrM;
@@ -986,15 +1009,8 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
   if constexpr (PHASE == kPhaseCommon) {
     if (rare) return o;
   }
-  if (PHASE == kPhaseAll && __any(rare)) v.w = locate<D>(d, v.site);
-  if (rare && !kXmax) {
-    xmax = R(-1);
-#pragma unroll 1
-    for (int i = 0; i < Q; ++i) {
-      R xi, fi;
-      v.xfe(i, xi, fi);
-      xmax = fmax(xmax, xi);
-    }
+  if constexpr (PHASE == kPhaseAll && !kXmax) {
+    if (rare) v.sweep([&](int, R, R xi, R, R) { xmax = fmax(xmax, xi); });
   }
   // alpha_max = min over {f^eq_i < f_i} of f_i/(f_i - f^eq_i) = 1 + 1/max_i x_i
   // (definition after Eq. (7)); alpha_* = min(2, alpha_max) (Eq. (8)), and
@@ -1071,7 +1087,7 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
               }
             } else {
               R dS, sA;
-              S_dS_newton(v, d, a, xabs, Sv, dS, sA);
+              S_dS_newton(v, a, xabs, Sv, dS, sA);
             }
             Ga = Sv - Dv;
           }
@@ -1094,7 +1110,7 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
       for (int k = 0; k <= d.root_max_iter; ++k) {
         const R a = k == 0 ? amax : R(0.5) * (lo + hi);
         R Sv, dS, sA;
-        S_dS_newton(v, d, a, xabs, Sv, dS, sA);
+        S_dS_newton(v, a, xabs, Sv, dS, sA);
         const R g = Sv - Dv;
         if (k == 0) {
           if (g <= R(0)) {
@@ -1131,7 +1147,7 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
       alpha = R(-1);
       for (int k = 1; k <= d.root_max_iter; ++k) {
         R Sv, dS, sA;
-        S_dS_newton(v, d, a, xabs, Sv, dS, sA);
+        S_dS_newton(v, a, xabs, Sv, dS, sA);
         const R gv = Sv - Dv;
         iters = k;
         if (fabs(gv) <= R(kEpsF64) * (R(1) + fabs(R(1) - a)) * sA) {
@@ -1151,7 +1167,6 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
             break;
           }
           if (!hi_pos) {
-            v.w = locate<D>(d, v.site);
             if (S_log(v, hi) - Dv <= R(0)) {
               alpha = hi;
               break;
@@ -1895,19 +1910,16 @@ __device__ __forceinline__ uint32_t site_update_rare_dev(const SimDesc& d, const
   float tmin = INFINITY;
   const uint32_t lo = (s & 63u) * es;
   const gaddr blk = block_base<Q>(dst, s);
-#pragma unroll 1
-  for (int i = 0; i < Q; ++i) {
-    float si, seqi;
-    v.sq(i, si, seqi);
+  v.sweep_dev([&](int i, float si, float seqi, double W) {
     const float sn = fmaf(ab, seqi - si, si);
     tmin = fminf(tmin, v.r + sn);
     T out;
     if constexpr (S::dev)
       out = T(sn);
     else
-      out = SiteDev<D, S>::enc_f(SiteDev<D, S>::weight_of(i), SiteDev<D, S>::weight_lo(i), v.r, sn);
+      out = SiteDev<D, S>::enc_f(float(W), SiteDev<D, S>::w_lo(W), v.r, sn);
     st_nt<T>(blk + (uint64_t)i * kLane * es, kLane * es, lo, out);
-  }
+  });
   return record_site<SUMS>(d, s, live, v, ao, double(tmin), j, acc, diag);
 }
 
@@ -1936,24 +1948,27 @@ __device__ __forceinline__ uint32_t site_update_rare_fp(const SimDesc& d, const 
   const gaddr blk = block_base<Q>(dst, s);
   const R ab = ao.alpha * (R)d.beta;
   R ftmin = R(INFINITY);
-#pragma unroll 1
-  for (int i = 0; i < Q; ++i) {
-    R xi, fi, gi;
-    v.xfe(i, xi, fi, &gi);
+  v.sweep([&](int i, R invW, R, R fi, R gi) {
     const R ft = fma(ab, fi - gi, gi);
     ftmin = fmin(ftmin, ft);
-    const int nz0 = (i % 3 == 0) + (D > 1 && (i / 3) % 3 == 0) + (D > 2 && i / 9 == 0);
-    const R invW = R(L::den()) / R(nz0 == 0 ? 1.0 : nz0 == 1 ? 4.0 : nz0 == 2 ? 16.0 : 64.0);
     st_nt<T>(blk + (uint64_t)i * kLane * es, kLane * es, lo, Codec<S, R>::enc(ft, invW, v.rho_ref));
-  }
+  });
   return record_site<SUMS>(d, s, live, v, ao, ftmin, j, acc, diag);
 }
 
 // A lane deferred by the common phase: the populations are reloaded (from
 // the caches, which this wavefront has just filled), the moments and the
 // equilibrium recomputed by the same arithmetic, alpha taken from the rare
-// tier, and the collision run as a rolled loop that re-reads each
-// population, so no per-direction array stays live across the logarithms.
+// tier, and the collision run as one more sweep().  What bounds it is
+// latency: with few rare wavefronts nothing hides theirs, and the launch
+// waits for the last.  When every pass re-read one population at a time, its
+// four passes were four times Q dependent cache latencies; sweeping the
+// registers (or three loads together with 27 directions) and folding the
+// passes that look for max|x_i| and max x_i into one took a burst of ten
+// 64^2 .. 512^2 shear-layer requests from 11.1 to 6.1 ms, a 133 x 727 FP32
+// vortex from 258 to 44 us (five steps) and D3Q27 100 x 90 x 70 in FP64,
+// where the first step finds every site there, from 765 to 490 us (four
+// steps with their reading); same bits.
 template <int D, class S, int MODE, class AP, bool SUMS>
 __device__ __forceinline__ uint32_t site_update_rare(const SimDesc& d,
                                                  const typename S::T* __restrict__ src,
@@ -2019,7 +2034,26 @@ __global__ void __launch_bounds__(kBlock, (step_waves<S, MODE>())) k_step(const 
   const uint32_t unit = (lb & 7u) * chunk + (lb >> 3);  // this workgroup's tile group
   Acc acc;
   acc.init();
-  if (unit * ELBM_TILES * kBlock < N) {
+  constexpr bool kRoot = MODE == kNewton || MODE == kBisect || MODE == kSecant;
+  if (unit * ELBM_TILES * kBlock >= N) {
+    if (!(diag & kDiagCounts)) return;  // padding workgroup
+  } else if constexpr (kRoot) {
+    // The root solvers are bound by their arithmetic: tile after tile in a
+    // rolled loop, one copy of the solver's passes in the instruction cache
+    // and one tile's populations in registers.
+#pragma unroll 1
+    for (int k = 0; k < ELBM_TILES; ++k) {
+      uint32_t flags = 0;
+      if ((unit * ELBM_TILES + k) * kBlock < N) {
+        const uint32_t s = (unit * ELBM_TILES + k) * kBlock + threadIdx.x;
+        Slot<T> raw[Q];
+        if (d.nx % 64 == 0) load_site_row<D>(d, src, s < N ? s : 0u, raw);
+        else load_site<D>(d, src, s < N ? s : 0u, raw);
+        flags = site_update<D, S, MODE, R, SUMS>(d, src, dst, s, s < N, raw, acc, diag).flags;
+      }
+      if (diag & kDiagCounts) acc.count_flags(flags);
+    }
+  } else {
     Slot<T> raw[ELBM_TILES][Q];
 #if ELBM_LOAD_PRIO
     __builtin_amdgcn_s_setprio(ELBM_LOAD_PRIO);
@@ -2098,11 +2132,8 @@ __global__ void __launch_bounds__(kBlock, (step_waves<S, MODE>())) k_step(const 
       }
       if (ELBM_TILES == 1 && (diag & kDiagCounts)) acc.count_flags(flags);
     }
-  } else if (!(diag & kDiagCounts)) {
-    return;  // padding workgroup
   }
-  if (diag & kDiagCounts)
-    store_records<MODE == kNewton || MODE == kBisect || MODE == kSecant>(acc, d, (int)lb);
+  if (diag & kDiagCounts) store_records<kRoot>(acc, d, (int)lb);
 }
 
 // The sums of ELBM_DIAG_SUMS (which need logarithms per site) are compiled

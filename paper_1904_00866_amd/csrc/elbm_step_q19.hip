@@ -68,7 +68,6 @@ struct SiteQ19 {
   const T* src;
   uint32_t site;
   const SimDesc* desc;
-  Where w;
 
   __device__ __forceinline__ R g(int i) const {
     return Codec<S, R>::dec_wide(widen<R>(raw[i]), R(L::W(i)), rho_ref);
@@ -171,23 +170,33 @@ struct SiteQ19 {
     return h;
   }
 
-  // run-time (wavefront-uniform) i: the population is re-read from the
-  // source buffer, as on the tensor-product lattices
+  // One pass f(i, 1/W_i, x_i, f^eq_i, g_i) for the rare tier, the root
+  // solvers' log1p passes and the collision (see Site::sweep): one direction
+  // at a time, re-read from the caches.  Rows of three together, as with 27
+  // directions, spill twice as many registers (the nine rows are not alike,
+  // so the body exists twice) and cost the Newton mode 12 %.
+  __device__ __forceinline__ static R sel9(const R (&a)[3][3], int dx, int dy) {
+    return sel3(a[0], dy) * R(dx == 0) + sel3(a[1], dy) * R(dx == 1) + sel3(a[2], dy) * R(dx == 2);
+  }
   __device__ __forceinline__ R fsel(int dx, int dy, int dz) const {
     return dz == 0 ? sel9(F0, dx, dy) : sel9(F1, dx, dy) * sel3(e2, dz);
   }
-  __device__ __forceinline__ void xfe(int i, R& xi, R& fi, R* gout = nullptr) const {
-    const int j = L::q27(i);
-    const int dx = j % 3, dy = (j / 3) % 3, dz = j / 9;
-    const int n = (dx != 0) + (dy != 0) + (dz != 0);
-    const R W = n == 0 ? R(1.0 / 3.0) : n == 1 ? R(1.0 / 18.0) : R(1.0 / 36.0);
-    const uint32_t sp = sel3(w.zs, dz) + sel3(w.ys, dy) + sel3(w.xs, dx);
-    const T gv = *(const gptr<T>)((gaddr)(uintptr_t)src + pidx<Q>(sp, i) * sizeof(T));
-    const R gi = Codec<S, R>::dec(gv, W, rho_ref);
-    fi = fsel(dx, dy, dz);
-    const R rf = fsel(opp(dx), opp(dy), opp(dz)) * sel3(kap, n);
-    xi = fma(gi, rf, R(-1));
-    if (gout) *gout = gi;
+  template <class F>
+  __device__ __forceinline__ void sweep(const F& f) const {
+    const Where w = locate<3>(*desc, site);
+#pragma unroll 1
+    for (int i = 0; i < Q; ++i) {
+      const int j = L::q27(i);
+      const int dx = j % 3, dy = (j / 3) % 3, dz = j / 9;
+      const int n = (dx != 0) + (dy != 0) + (dz != 0);
+      const R W = n == 0 ? R(1.0 / 3.0) : n == 1 ? R(1.0 / 18.0) : R(1.0 / 36.0);
+      const R iW = n == 0 ? R(3) : n == 1 ? R(18) : R(36);
+      const uint32_t sp = sel3(w.zs, dz) + sel3(w.ys, dy) + sel3(w.xs, dx);
+      const T gv = *(const gptr<T>)((gaddr)(uintptr_t)src + pidx<Q>(sp, i) * sizeof(T));
+      const R gi = Codec<S, R>::dec(gv, W, rho_ref);
+      const R rf = fsel(opp(dx), opp(dy), opp(dz)) * sel3(kap, n);
+      f(i, iW, fma(gi, rf, R(-1)), fsel(dx, dy, dz), gi);
+    }
   }
 };
 
@@ -395,17 +404,11 @@ __device__ __forceinline__ uint32_t update_rare_q19(const SimDesc& d,
   R ftmin = R(INFINITY);
   const uint32_t lo = (s & 63u) * es;
   const gaddr blk = block_base<Q>(dst, s);
-#pragma unroll 1
-  for (int i = 0; i < Q; ++i) {
-    R xi, fi, gi;
-    v.xfe(i, xi, fi, &gi);
+  v.sweep([&](int i, R invW, R, R fi, R gi) {
     const R ft = fma(ab, fi - gi, gi);
     ftmin = fmin(ftmin, ft);
-    const int jj = L19::q27(i);
-    const int n = (jj % 3 != 0) + ((jj / 3) % 3 != 0) + (jj / 9 != 0);
-    const R invW = n == 0 ? R(3) : n == 1 ? R(18) : R(36);
     st_nt<T>(blk + (uint64_t)i * kLane * es, kLane * es, lo, Codec<S, R>::enc(ft, invW, v.rho_ref));
-  }
+  });
   return record_site<SUMS>(d, s, live, v, ao, ftmin, j, acc, diag);
 }
 
