@@ -242,6 +242,8 @@ BoxDesc box_of(const elbm_sim* s) {
   b.N = s->L.N;
   b.padded = s->L.padded;
   b.rho_ref = s->cfg.rho_ref;
+  b.inv_nx = 1.0 / double(b.nx);
+  b.inv_ny = 1.0 / double(b.ny);
   return b;
 }
 

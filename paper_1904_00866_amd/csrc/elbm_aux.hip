@@ -7,6 +7,7 @@
 // step before streaming (Eq. (5b) is carried out by the reader).
 #include "elbm_internal.hpp"
 #include "elbm_burg.hpp"
+#include "elbm_pull.hpp"
 #include "elbm_q19.hpp"
 #include "elbm_site.hpp"
 
@@ -14,30 +15,37 @@ namespace elbm {
 
 namespace {
 
-struct Coord {
-  int64_t x, y, z;
-};
+// What bounds the readings below is their traffic: Q populations in, D + 1 or
+// Q doubles out, each once.  One thread per site in the step kernel's XCD
+// order (a run of 64 shifted by one site reaches into the next block's line,
+// which is then in the same L2), with its row-descriptor loads where a
+// wavefront's sites lie in one x-row and 32-bit site coordinates.  With
+// 64-bit divisions per direction and blocks dealt round the XCDs the moments
+// of a 512^3 FP32 box took 4.2 ms, now 3.5 ms (5.3 TB/s); 256^3 in FP16,
+// 0.56 -> 0.27 ms.
 
-__device__ __forceinline__ Coord coord_of(const BoxDesc& b, int64_t s) {
-  Coord c;
-  c.x = s % b.nx;
-  const int64_t r = s / b.nx;
-  c.y = r % b.ny;
-  c.z = r / b.ny;
-  return c;
+// Site of this thread: workgroup b of a grid that is a multiple of 8 takes
+// block (b mod 8) grid / 8 + b / 8, so that each XCD has one contiguous eighth.
+__device__ __forceinline__ uint32_t site_of_thread() {
+  const uint32_t b = blockIdx.x, chunk = gridDim.x >> 3;
+  return ((b & 7u) * chunk + (b >> 3)) * blockDim.x + threadIdx.x;
 }
 
-__device__ __forceinline__ int64_t wrapi(int64_t v, int64_t n) {
-  return v < 0 ? v + n : (v >= n ? v - n : v);
+// The pre-collision populations of site s, as stored.
+template <class L, class T>
+__device__ __forceinline__ void pull(const BoxDesc& b, const T* buf, uint32_t s, T (&raw)[L::Q]) {
+  if (b.nx % kLane == 0) load_row_l<L>(b, buf, s, raw);
+  else load_l<L>(b, buf, s, raw);
 }
 
-// site index of x - c_i
-template <class L>
-__device__ __forceinline__ int64_t upstream(const BoxDesc& b, const Coord& c, int i) {
-  const int64_t x = wrapi(c.x - L::c(i, 0), b.nx);
-  const int64_t y = wrapi(c.y - L::c(i, 1), b.ny);
-  const int64_t z = wrapi(c.z - L::c(i, 2), b.nz);
-  return x + b.nx * (y + b.ny * z);
+// Site index of x - c_i (sign = +1) or x + c_i (sign = -1).
+template <class L, int SIGN>
+__device__ __forceinline__ uint32_t neighbour(const Where& w, int i) {
+  const auto dg = [&](int a) {
+    const int k = L::dg(i, a);
+    return SIGN > 0 || k == 0 ? k : 3 - k;
+  };
+  return w.zs[dg(2)] + w.ys[dg(1)] + w.xs[dg(0)];
 }
 
 // rho0 > 0 and u0 inside the hull of the velocities: |u_a| < 1, and on
@@ -59,53 +67,81 @@ __global__ void k_validate(int64_t N, int D, int hull2, const double* __restrict
   if ((threadIdx.x & 63) == 0 && nb) atomicAdd(bad, (unsigned long long)__popcll(nb));
 }
 
+// f^eq(rho0, u0) in pull convention: f_i of site x goes to x - c_i.
 template <class L, class S>
-__global__ void k_scatter(const BoxDesc b, typename S::T* __restrict__ buf,
-                          const double* __restrict__ rho0, const double* __restrict__ u0,
-                          const double* __restrict__ f, int which) {
+__global__ void k_init(const BoxDesc b, typename S::T* __restrict__ buf,
+                       const double* __restrict__ rho0, const double* __restrict__ u0) {
   constexpr int D = L::Dim;
   constexpr int Q = L::Q;
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t s = site_of_thread();
   if (s >= b.N) return;
-  const Coord c = coord_of(b, s);
   double fv[Q];
-  if (which == 0) {
-    double u[3] = {0.0, 0.0, 0.0};
-    for (int a = 0; a < D; ++a) u[a] = u0[a * b.N + s];
-    if (b.entropy == 1) {
-      // Burg's entropy: f^eq_i = W_i / d_i (elbm_burg.hpp)
-      double mu[4];
-      burg_multipliers<L>(rho0[s], 1.0 / rho0[s], u, mu);
+  double u[3] = {0.0, 0.0, 0.0};
+  for (int a = 0; a < D; ++a) u[a] = u0[a * b.N + s];
+  if (b.entropy == 1) {
+    // Burg's entropy: f^eq_i = W_i / d_i (elbm_burg.hpp)
+    double mu[4];
+    burg_multipliers<L>(rho0[s], 1.0 / rho0[s], u, mu);
 #pragma unroll
-      for (int i = 0; i < Q; ++i) fv[i] = L::W(i) / burg_den<L>(mu, i);
-    } else if constexpr (Q == 19) {
-      // f^eq_i = rho W_i prod_a X_a^c_ia / Z  (EquilibriumQ19)
-      EquilibriumQ19<double> eq;
-      eq.build(u);
-      const double cF = rho0[s] / eq.Z9;
+    for (int i = 0; i < Q; ++i) fv[i] = L::W(i) / burg_den<L>(mu, i);
+  } else if constexpr (Q == 19) {
+    // f^eq_i = rho W_i prod_a X_a^c_ia / Z  (EquilibriumQ19)
+    EquilibriumQ19<double> eq;
+    eq.build(u);
+    const double cF = rho0[s] / eq.Z9;
 #pragma unroll
-      for (int i = 0; i < Q; ++i) {
-        double p = cF * (9.0 * L::W(i));
+    for (int i = 0; i < Q; ++i) {
+      double p = cF * (9.0 * L::W(i));
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
-          p *= L::dg(i, a) == 0 ? 1.0 : (L::dg(i, a) == 1 ? eq.X[a] : eq.Y[a]);
-        fv[i] = p;
-      }
-    } else {
-      Equilibrium<double, D> eq;
-      eq.build(u);
-#pragma unroll
-      for (int i = 0; i < Q; ++i)
-        fv[i] = rho0[s] * (eq.e(0, L::dg(i, 0)) * eq.e(1, L::dg(i, 1))) * eq.e(2, L::dg(i, 2));
+      for (int a = 0; a < 3; ++a)
+        p *= L::dg(i, a) == 0 ? 1.0 : (L::dg(i, a) == 1 ? eq.X[a] : eq.Y[a]);
+      fv[i] = p;
     }
   } else {
+    Equilibrium<double, D> eq;
+    eq.build(u);
 #pragma unroll
-    for (int i = 0; i < Q; ++i) fv[i] = f[i * b.N + s];
+    for (int i = 0; i < Q; ++i)
+      fv[i] = rho0[s] * (eq.e(0, L::dg(i, 0)) * eq.e(1, L::dg(i, 1))) * eq.e(2, L::dg(i, 2));
   }
+  const Where w = locate<D>(b, s);
 #pragma unroll
   for (int i = 0; i < Q; ++i)
-    buf[pidx<Q>(upstream<L>(b, c, i), i)] =
+    buf[pidx<Q>(neighbour<L, 1>(w, i), i)] =
         Codec<S, double>::enc(fv[i], L::invW(i), b.rho_ref);
+}
+
+// Given f(x, t) in pull convention: each stored element (i, y) takes
+// f_i(y + c_i), so that the writes are whole blocks and the reads carry the
+// shifts.
+template <class L, class S>
+__global__ void k_put(const BoxDesc b, typename S::T* __restrict__ buf,
+                      const double* __restrict__ f) {
+  constexpr int Q = L::Q;
+  const uint32_t s = site_of_thread();
+  if (s >= b.N) return;
+  const Where w = locate<L::Dim>(b, s);
+  double fv[Q];
+#pragma unroll
+  for (int i = 0; i < Q; ++i) fv[i] = f[i * b.N + neighbour<L, -1>(w, i)];
+#pragma unroll
+  for (int i = 0; i < Q; ++i)
+    buf[pidx<Q>(s, i)] = Codec<S, double>::enc(fv[i], L::invW(i), b.rho_ref);
+}
+
+// f(x, t) of every site.
+template <class L, class S>
+__global__ void k_populations(const BoxDesc b, const typename S::T* __restrict__ buf,
+                              double* __restrict__ out) {
+  constexpr int Q = L::Q;
+  const uint32_t s = site_of_thread();
+  if (s >= b.N) return;
+  typename S::T raw[Q];
+  pull<L>(b, buf, s, raw);
+#pragma unroll
+  for (int i = 0; i < Q; ++i)
+    __builtin_nontemporal_store(Codec<S, double>::dec(raw[i], L::W(i), b.rho_ref),
+                                out + i * b.N + s);
 }
 
 template <class L, class S>
@@ -115,15 +151,15 @@ __global__ void k_gather(const BoxDesc b, const typename S::T* __restrict__ buf,
   constexpr int Q = L::Q;
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
-  const int64_t s = sites ? sites[k] : k;
+  const int64_t s = sites[k];
   if (s < 0 || s >= b.N) {
     for (int i = 0; i < Q; ++i) out[i * n + k] = NAN;
     return;
   }
-  const Coord c = coord_of(b, s);
+  const Where w = locate<L::Dim>(b, (uint32_t)s);
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
-    const int64_t src = which == 0 ? upstream<L>(b, c, i) : s;
+    const uint32_t src = which == 0 ? neighbour<L, 1>(w, i) : (uint32_t)s;
     out[i * n + k] = Codec<S, double>::dec(buf[pidx<Q>(src, i)], L::W(i), b.rho_ref);
   }
 }
@@ -133,63 +169,122 @@ __global__ void k_moments(const BoxDesc b, const typename S::T* __restrict__ buf
                           double* __restrict__ rho, double* __restrict__ u) {
   constexpr int D = L::Dim;
   constexpr int Q = L::Q;
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t s = site_of_thread();
   if (s >= b.N) return;
-  const Coord c = coord_of(b, s);
+  typename S::T raw[Q];
+  pull<L>(b, buf, s, raw);
   double r = 0.0, j[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
-    const double g = Codec<S, double>::dec(buf[pidx<Q>(upstream<L>(b, c, i), i)], L::W(i), b.rho_ref);
+    const double g = Codec<S, double>::dec(raw[i], L::W(i), b.rho_ref);
     r += g;
-    for (int a = 0; a < D; ++a) j[a] += L::c(i, a) * g;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      if (L::c(i, a) > 0) j[a] += g;
+      else if (L::c(i, a) < 0) j[a] -= g;
+    }
   }
   rho[s] = r;
-  for (int a = 0; a < D; ++a) u[a * b.N + s] = j[a] / r;
+  // a NaN or an infinity among the populations leaves no velocity component
+  // defined, also those that its direction does not enter
+#pragma unroll
+  for (int a = 0; a < D; ++a) u[a * b.N + s] = isfinite(r) ? j[a] / r : NAN;
 }
 
-// Fixed-order reduction of the per-workgroup records: thread t folds records
-// t, t + kBlock, ... in order, then a fixed tree combines the threads.
-__global__ void k_reduce(const CountRec* __restrict__ cr, const SumRec* __restrict__ sr, int n,
-                         Reduced* __restrict__ out) {
-  __shared__ double sd[kBlock][5];
-  __shared__ float sa[kBlock][2];
-  __shared__ unsigned long long sc[kBlock][kNumCounts];
-  const int t = threadIdx.x;
-  double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  float mn = INFINITY, mx = -INFINITY;
+// Fixed-order reduction of the per-workgroup records by one workgroup per
+// chunk of them: thread t folds the chunk's records t, t + kBlock, ... in
+// order, then a fixed tree combines the threads.  A box of many workgroups
+// is folded in two launches (one workgroup over the 524,288 records of 512^3
+// takes 1.1 ms; the two launches 17 us): the first leaves the kPartWords
+// 64-bit words of each chunk's result in the pad words of the chunk's own
+// first records (which every step writes as zero and nothing else reads), the
+// second folds those.
+struct Partial {
   unsigned long long c[kNumCounts];
-  for (int m = 0; m < kNumCounts; ++m) c[m] = 0;
-  for (int k = t; k < n; k += kBlock) {
-    const CountRec& q = cr[k];
-    for (int m = 0; m < kNumCounts; ++m) c[m] += q.cnt[m];
-    mn = fminf(mn, q.amin);
-    mx = fmaxf(mx, q.amax);
-    if (sr) {
-      const SumRec& w = sr[k];
-      v[0] += w.rho; v[1] += w.j[0]; v[2] += w.j[1]; v[3] += w.j[2]; v[4] += w.H;
+  double v[5];
+  float mn, mx;
+};
+constexpr int kPartWords = sizeof(Partial) / 8;
+static_assert(sizeof(Partial) == 8 * kPartWords && sizeof(CountRec::pad) == 8,
+              "a partial result is spread over the records' 8-byte pads");
+constexpr int kOneLaunch = 4096;  // records up to which one workgroup folds them alone
+constexpr int kMaxParts = kBlock;
+
+__device__ __forceinline__ void fold(Partial& p, const Partial& q) {
+#pragma unroll
+  for (int m = 0; m < kNumCounts; ++m) p.c[m] += q.c[m];
+#pragma unroll
+  for (int m = 0; m < 5; ++m) p.v[m] += q.v[m];
+  p.mn = fminf(p.mn, q.mn);
+  p.mx = fmaxf(p.mx, q.mx);
+}
+
+// PARTS: fold the partial results of ceil(n / chunk) chunks; else the
+// records of chunk blockIdx.x.  With `out`, the result goes there, otherwise
+// into the pads of the chunk.
+template <bool PARTS>
+__global__ void k_reduce(CountRec* __restrict__ cr, const SumRec* __restrict__ sr, int n,
+                         int chunk, Reduced* __restrict__ out) {
+  __shared__ Partial sp[kBlock / 64];
+  const int t = threadIdx.x;
+  Partial p{};
+  p.mn = INFINITY;
+  p.mx = -INFINITY;
+  if constexpr (PARTS) {
+    if ((int64_t)t * chunk < n) {
+      unsigned long long w[kPartWords];
+#pragma unroll
+      for (int m = 0; m < kPartWords; ++m)
+        w[m] = *reinterpret_cast<const unsigned long long*>(cr[t * chunk + m].pad);
+      __builtin_memcpy(&p, w, sizeof p);
+    }
+  } else {
+    const int k0 = blockIdx.x * chunk, k1 = min(n, k0 + chunk);
+    for (int k = k0 + t; k < k1; k += kBlock) {
+      const CountRec& q = cr[k];
+      Partial w{};
+#pragma unroll
+      for (int m = 0; m < kNumCounts; ++m) w.c[m] = q.cnt[m];
+      w.mn = q.amin;
+      w.mx = q.amax;
+      if (sr) {
+        const SumRec& z = sr[k];
+        w.v[0] = z.rho; w.v[1] = z.j[0]; w.v[2] = z.j[1]; w.v[3] = z.j[2]; w.v[4] = z.H;
+      }
+      fold(p, w);
     }
   }
-  for (int m = 0; m < 5; ++m) sd[t][m] = v[m];
-  sa[t][0] = mn;
-  sa[t][1] = mx;
-  for (int m = 0; m < kNumCounts; ++m) sc[t][m] = c[m];
+  // the wavefront's 64 partial results by a shuffle tree, then the wavefronts
+  // in order
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    Partial q;
+#pragma unroll
+    for (int m = 0; m < kNumCounts; ++m) q.c[m] = __shfl_down(p.c[m], o);
+#pragma unroll
+    for (int m = 0; m < 5; ++m) q.v[m] = __shfl_down(p.v[m], o);
+    q.mn = __shfl_down(p.mn, o);
+    q.mx = __shfl_down(p.mx, o);
+    fold(p, q);
+  }
+  if ((t & 63) == 0) sp[t >> 6] = p;
   __syncthreads();
-  for (int w = kBlock / 2; w > 0; w >>= 1) {
-    if (t < w) {
-      for (int m = 0; m < 5; ++m) sd[t][m] += sd[t + w][m];
-      sa[t][0] = fminf(sa[t][0], sa[t + w][0]);
-      sa[t][1] = fmaxf(sa[t][1], sa[t + w][1]);
-      for (int m = 0; m < kNumCounts; ++m) sc[t][m] += sc[t + w][m];
-    }
-    __syncthreads();
-  }
-  if (t == 0) {
-    for (int m = 0; m < kNumCounts; ++m) out->cnt[m] = (int64_t)sc[0][m];
-    out->amin = sa[0][0];
-    out->amax = sa[0][1];
-    out->rho = sd[0][0];
-    out->j[0] = sd[0][1]; out->j[1] = sd[0][2]; out->j[2] = sd[0][3];
-    out->H = sd[0][4];
+  if (t != 0) return;
+  for (int w = 1; w < kBlock / 64; ++w) fold(p, sp[w]);
+  if (out) {
+    for (int m = 0; m < kNumCounts; ++m) out->cnt[m] = (int64_t)p.c[m];
+    out->amin = p.mn;
+    out->amax = p.mx;
+    out->rho = p.v[0];
+    out->j[0] = p.v[1]; out->j[1] = p.v[2]; out->j[2] = p.v[3];
+    out->H = p.v[4];
+  } else {
+    unsigned long long w[kPartWords];
+    __builtin_memcpy(w, &p, sizeof p);
+    CountRec* c0 = cr + (int64_t)blockIdx.x * chunk;
+#pragma unroll
+    for (int m = 0; m < kPartWords; ++m)
+      *reinterpret_cast<unsigned long long*>(c0[m].pad) = w[m];
   }
 }
 
@@ -199,6 +294,8 @@ __global__ void k_copy_f64(const double* __restrict__ a, double* __restrict__ b,
 }
 
 inline unsigned grid_for(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
+// a multiple of 8 workgroups (site_of_thread)
+inline unsigned grid_for_box(const BoxDesc& b) { return (grid_for(b.N, 256) + 7) / 8 * 8; }
 
 // lattice: 1, 2, 3 (D1Q3, D2Q9, D3Q27) or 19 (D3Q19)
 template <template <class, class> class Fn, class... A>
@@ -226,8 +323,9 @@ struct ScatterFn {
   static hipError_t run(const BoxDesc& b, void* buf, const double* rho0, const double* u0,
                         const double* f, int which, hipStream_t st) {
     if (b.N == 0) return hipSuccess;
-    k_scatter<L, S><<<grid_for(b.N, 256), 256, 0, st>>>(b, static_cast<typename S::T*>(buf),
-                                                       rho0, u0, f, which);
+    auto* p = static_cast<typename S::T*>(buf);
+    if (which == 0) k_init<L, S><<<grid_for_box(b), 256, 0, st>>>(b, p, rho0, u0);
+    else k_put<L, S><<<grid_for_box(b), 256, 0, st>>>(b, p, f);
     return hipGetLastError();
   }
 };
@@ -237,8 +335,9 @@ struct GatherFn {
   static hipError_t run(const BoxDesc& b, const void* buf, const int64_t* sites, int64_t n,
                         int which, double* out, hipStream_t st) {
     if (n == 0) return hipSuccess;
-    k_gather<L, S><<<grid_for(n, 256), 256, 0, st>>>(b, static_cast<const typename S::T*>(buf),
-                                                    sites, n, which, out);
+    const auto* p = static_cast<const typename S::T*>(buf);
+    if (!sites) k_populations<L, S><<<grid_for_box(b), 256, 0, st>>>(b, p, out);
+    else k_gather<L, S><<<grid_for(n, 256), 256, 0, st>>>(b, p, sites, n, which, out);
     return hipGetLastError();
   }
 };
@@ -248,8 +347,8 @@ struct MomentsFn {
   static hipError_t run(const BoxDesc& b, const void* buf, double* rho, double* u,
                         hipStream_t st) {
     if (b.N == 0) return hipSuccess;
-    k_moments<L, S><<<grid_for(b.N, 256), 256, 0, st>>>(b, static_cast<const typename S::T*>(buf),
-                                                       rho, u);
+    k_moments<L, S><<<grid_for_box(b), 256, 0, st>>>(b, static_cast<const typename S::T*>(buf),
+                                                     rho, u);
     return hipGetLastError();
   }
 };
@@ -278,10 +377,23 @@ hipError_t launch_moments(const BoxDesc& b, const void* buf, double* rho, double
   return dispatch<MomentsFn>(b.lattice, b.storage, b, buf, rho, u, st);
 }
 
-hipError_t launch_reduce(const void* counts, const void* sums, int nblocks, Reduced* out,
+hipError_t launch_reduce(void* counts, const void* sums, int nblocks, Reduced* out,
                          hipStream_t st) {
-  k_reduce<<<1, kBlock, 0, st>>>(static_cast<const CountRec*>(counts),
-                                 static_cast<const SumRec*>(sums), nblocks, out);
+  auto* cr = static_cast<CountRec*>(counts);
+  const auto* sr = static_cast<const SumRec*>(sums);
+  if (nblocks <= kOneLaunch) {
+    k_reduce<false><<<1, kBlock, 0, st>>>(cr, sr, nblocks, nblocks, out);
+    return hipGetLastError();
+  }
+  // at least kOneLaunch / kMaxParts records a chunk; the last may be short,
+  // but never shorter than a partial result
+  static_assert(kOneLaunch / kMaxParts >= kPartWords, "a chunk's pads hold its result");
+  int parts = kMaxParts;
+  int chunk = (nblocks + parts - 1) / parts;
+  while ((nblocks - 1) % chunk + 1 < kPartWords) ++chunk;
+  parts = (nblocks + chunk - 1) / chunk;
+  k_reduce<false><<<parts, kBlock, 0, st>>>(cr, sr, nblocks, chunk, nullptr);
+  k_reduce<true><<<1, kBlock, 0, st>>>(cr, nullptr, nblocks, chunk, out);
   return hipGetLastError();
 }
 

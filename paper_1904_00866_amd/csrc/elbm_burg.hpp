@@ -5,30 +5,11 @@
 // the Lagrangian makes h'(f^eq_i) = -W_i / f^eq_i affine in (1, c_i)).
 #pragma once
 
+#include "elbm_pull.hpp"
 #include "elbm_q19.hpp"
 #include "elbm_site.hpp"
 
 namespace elbm {
-
-// Direction index of the digits (dx, dy, dz) on lattice L, or -1 if L has
-// no such direction.
-template <class L>
-struct Dirs;
-template <int D>
-struct Dirs<Lattice<D>> {
-  static constexpr int index(int dx, int dy, int dz) {
-    return ((D < 2 && dy != 0) || (D < 3 && dz != 0)) ? -1 : dx + 3 * dy + 9 * dz;
-  }
-};
-template <>
-struct Dirs<LatticeQ19> {
-  static constexpr int index(int dx, int dy, int dz) {
-    return (dx != 0 && dy != 0 && dz != 0)
-               ? -1
-               : (dx + 3 * dy + 9 * dz) - 2 * ((dx + 3 * dy + 9 * dz) >= 13) -
-                     2 * ((dx + 3 * dy + 9 * dz) >= 18) - 2 * ((dx + 3 * dy + 9 * dz) >= 22);
-  }
-};
 
 // Index of the direction -c_i (digits 1 and 2 swapped).
 template <class L>

@@ -120,6 +120,7 @@ struct BoxDesc {
   int32_t nx, ny, nz;
   int64_t N, padded;
   double rho_ref;
+  double inv_nx, inv_ny;  // 1/nx, 1/ny for the site-coordinate quotients
 };
 hipError_t launch_validate_init(const BoxDesc& b, const double* rho0, const double* u0,
                                 unsigned long long* bad, hipStream_t st);
@@ -131,7 +132,9 @@ hipError_t launch_gather(const BoxDesc& b, const void* buf, const int64_t* sites
                          int which, double* out, hipStream_t st);
 hipError_t launch_moments(const BoxDesc& b, const void* buf, double* rho, double* u,
                           hipStream_t st);
-hipError_t launch_reduce(const void* counts, const void* sums, int nblocks, Reduced* out,
+// Folds the nblocks per-workgroup records into *out.  The pad words of the
+// count records are its scratch.
+hipError_t launch_reduce(void* counts, const void* sums, int nblocks, Reduced* out,
                          hipStream_t st);
 hipError_t launch_copy_f64(const double* src, double* dst, int64_t n, hipStream_t st);
 

@@ -28,61 +28,6 @@
 namespace elbm {
 namespace {
 
-// Pull of the Q populations when the wavefront's 64 sites lie in one x-row
-// (one descriptor per source row (c_y, c_z); see load_site_row).
-template <class L, class T>
-__device__ __forceinline__ void load_row_l(const SimDesc& d, const T* src, uint32_t s,
-                                           T (&raw)[L::Q]) {
-  constexpr int D = L::Dim, Q = L::Q;
-  const uint32_t nx = (uint32_t)d.nx, ny = (uint32_t)d.ny, nz = (uint32_t)d.nz;
-  const uint32_t row = __builtin_amdgcn_readfirstlane(D == 1 ? 0u : qdiv(s, d.inv_nx));
-  const uint32_t x = s - row * nx;
-  uint32_t ys[3] = {0u, 0u, 0u}, zs[3] = {0u, 0u, 0u};
-  if constexpr (D > 1) {
-    const uint32_t z = D == 3 ? __builtin_amdgcn_readfirstlane(qdiv(row, d.inv_ny)) : 0u;
-    const uint32_t y = row - z * ny;
-    ys[0] = y * nx;
-    ys[1] = (y == 0 ? ny - 1 : y - 1) * nx;
-    ys[2] = (y == ny - 1 ? 0 : y + 1) * nx;
-    const uint32_t nxy = nx * ny;
-    zs[0] = z * nxy;
-    zs[1] = (z == 0 ? nz - 1 : z - 1) * nxy;
-    zs[2] = (z == nz - 1 ? 0 : z + 1) * nxy;
-  }
-  constexpr uint32_t es = sizeof(T);
-  uint32_t xo[3];
-  const uint32_t xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
-  xo[0] = (uint32_t)pidx<Q>(x, 0) * es;
-  xo[1] = (uint32_t)pidx<Q>(xm, 0) * es;
-  xo[2] = (uint32_t)pidx<Q>(xp, 0) * es;
-  const gaddr base = buffer_base(src);
-  const uint32_t rowbytes = nx * (uint32_t)Q * es;
-#pragma unroll
-  for (int dz = 0; dz < (D > 2 ? 3 : 1); ++dz)
-#pragma unroll
-    for (int dy = 0; dy < (D > 1 ? 3 : 1); ++dy) {
-      const __amdgpu_buffer_rsrc_t r = rsrc(base + (uint64_t)(zs[dz] + ys[dy]) * Q * es, rowbytes);
-#pragma unroll
-      for (int dx = 0; dx < 3; ++dx) {
-        const int i = Dirs<L>::index(dx, dy, dz);
-        if (i < 0) continue;
-        raw[i] = ld_buf<T>(r, xo[dx], (uint32_t)i * kLane * es);
-      }
-    }
-}
-
-// Pull of the Q populations of site s (s < N), any box.
-template <class L, class T>
-__device__ __forceinline__ void load_l(const SimDesc& d, const T* src, uint32_t s, T (&raw)[L::Q]) {
-  const Where w = locate<L::Dim>(d, s);
-  const gaddr base = buffer_base(src);
-#pragma unroll
-  for (int i = 0; i < L::Q; ++i) {
-    const uint32_t sp = w.zs[L::dg(i, 2)] + w.ys[L::dg(i, 1)] + w.xs[L::dg(i, 0)];
-    raw[i] = *(const gptr<T>)(base + pidx<L::Q>(sp, i) * sizeof(T));
-  }
-}
-
 template <class L, class S>
 struct SiteBurg {
   using T = typename S::T;
