@@ -132,10 +132,11 @@ enum { ELBM_ARITH_FP32 = 0, ELBM_ARITH_FP64 = 1, ELBM_ARITH_MIXED = 2 };
  * storage. */
 enum { ELBM_ENTROPY_BOLTZMANN = 0, ELBM_ENTROPY_BURG = 1 };
 
-/* Diagnostics switches (bit mask). */
+/* Diagnostics switches (bit mask).  What is recorded belongs to the most
+ * recent step; of the steps of one call only the last records. */
 enum {
-  ELBM_DIAG_ALPHA = 1u,  /* record alpha(x) of every step (8 B/site extra) */
-  ELBM_DIAG_COUNTS = 2u, /* per-step site counts and the alpha range      */
+  ELBM_DIAG_ALPHA = 1u,  /* alpha(x) of the most recent step (8 B/site)    */
+  ELBM_DIAG_COUNTS = 2u, /* its site counts and the alpha range           */
   ELBM_DIAG_SUMS = 4u    /* also sum_x rho, rho u and H(f(x,t)) (Eq. (6)); */
                          /* needs COUNTS                                  */
 };

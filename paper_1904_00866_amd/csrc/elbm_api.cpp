@@ -247,7 +247,12 @@ BoxDesc box_of(const elbm_sim* s) {
   return b;
 }
 
-SimDesc desc_of(const elbm_sim* s, int block_begin) {
+// last: the last step of a call.  Only its diagnostics can be read
+// afterwards (each step's records overwrite the step's before), so the steps
+// before it record none: no alpha field written, no counts, no logarithms
+// for the sums (20 steps at 1024^2 with all three and
+// their readings: 800 -> 446 us).
+SimDesc desc_of(const elbm_sim* s, int block_begin, bool last) {
   SimDesc d;
   std::memset(&d, 0, sizeof d);
   d.src = s->buf[s->cur];
@@ -269,15 +274,16 @@ SimDesc desc_of(const elbm_sim* s, int block_begin) {
   d.block_begin = block_begin;
   d.root_max_iter = s->cfg.root_max_iter;
   d.secant_iters = s->cfg.secant_iters;
-  d.diag = int(s->cfg.diag);
+  d.diag = last ? int(s->cfg.diag) : 0;
   return d;
 }
 
-void after_step(elbm_sim* s) {
+// last: as for desc_of (a step that records nothing leaves nothing to read)
+void after_step(elbm_sim* s, bool last) {
   s->cur = 1 - s->cur;
   s->t += 1;
-  if (s->cfg.diag & ELBM_DIAG_ALPHA) s->have_alpha = true;
-  if (s->cfg.diag & ELBM_DIAG_COUNTS) s->have_stats = true;
+  s->have_alpha = last && (s->cfg.diag & ELBM_DIAG_ALPHA);
+  s->have_stats = last && (s->cfg.diag & ELBM_DIAG_COUNTS);
 }
 
 elbm_status check_sim(const elbm_sim* s) {
@@ -507,10 +513,10 @@ elbm_status elbm_step(elbm_sim* s, int64_t nsteps) {
   BatchArgs a;
   a.n = 1;
   for (int64_t k = 0; k < nsteps; ++k) {
-    a.d[0] = desc_of(s, 0);
+    a.d[0] = desc_of(s, 0, k == nsteps - 1);
     hipError_t e = s->launch(a, s->L.nblocks, s->stream);
     if (e != hipSuccess) return hip_fail(e, "step kernel launch");
-    after_step(s);
+    after_step(s, k == nsteps - 1);
   }
   return ELBM_OK;
 }
@@ -537,23 +543,29 @@ elbm_status elbm_step_batch(elbm_sim* const* sims, const int64_t* nsteps, int32_
   DeviceGuard g(s0->device);
   if (!g.ok) return fail(ELBM_EDEVICE, "cannot select the simulations' device");
   std::vector<elbm_sim*> active;
+  std::vector<char> last;  // this step is the simulation's last of the call
   active.reserve(size_t(n));
+  last.reserve(size_t(n));
   for (int64_t step = 0; step < kmax; ++step) {
     active.clear();
+    last.clear();
     for (int32_t k = 0; k < n; ++k)
-      if (nsteps[k] > step) active.push_back(sims[k]);
+      if (nsteps[k] > step) {
+        active.push_back(sims[k]);
+        last.push_back(nsteps[k] == step + 1);
+      }
     for (size_t c0 = 0; c0 < active.size(); c0 += kMaxBatch) {
       BatchArgs a;
       a.n = 0;
       int blocks = 0;
       const size_t c1 = std::min(active.size(), c0 + size_t(kMaxBatch));
       for (size_t k = c0; k < c1; ++k) {
-        a.d[a.n++] = desc_of(active[k], blocks);
+        a.d[a.n++] = desc_of(active[k], blocks, last[k]);
         blocks += active[k]->L.nblocks;
       }
       hipError_t e = s0->launch(a, blocks, s0->stream);
       if (e != hipSuccess) return hip_fail(e, "batched step kernel launch");
-      for (size_t k = c0; k < c1; ++k) after_step(active[k]);
+      for (size_t k = c0; k < c1; ++k) after_step(active[k], last[k]);
     }
   }
   return ELBM_OK;
@@ -583,13 +595,14 @@ elbm_status elbm_step_noalloc(elbm_sim* s, int64_t nsteps, uint32_t diag,
   BatchArgs a;
   a.n = 1;
   for (int64_t k = 0; k < nsteps; ++k) {
-    a.d[0] = desc_of(s, 0);
+    const bool last = k == nsteps - 1;
+    a.d[0] = desc_of(s, 0, last);
     a.d[0].counts = counts;
     a.d[0].sums = sums;
-    a.d[0].diag = int((s->cfg.diag & ELBM_DIAG_ALPHA) | diag);
+    a.d[0].diag = last ? int((s->cfg.diag & ELBM_DIAG_ALPHA) | diag) : 0;
     if ((e = s->launch(a, s->L.nblocks, s->stream)) != hipSuccess)
       return hip_fail(e, "step kernel launch");
-    after_step(s);
+    after_step(s, last);
   }
   // the handle's own records were not written by these steps
   s->have_stats = false;
