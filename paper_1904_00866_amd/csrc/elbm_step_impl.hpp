@@ -258,8 +258,10 @@ struct Site {
   // most of each other's latency).  With 27 directions the populations are
   // not kept through the logarithms (registers): a loop over the rows
   // (c_y, c_z) re-reads the three of each, together, from the caches this
-  // wavefront has just filled.
-  template <class F>
+  // wavefront has just filled.  So do the root solvers' passes on any lattice
+  // (REREAD), one direction at a time: their four unrolled tiles hold one
+  // body of the logarithms each, more would keep the tiles from unrolling.
+  template <bool REREAD = (D == 3), class F>
   __device__ __forceinline__ void sweep(const F& f) const {
     if constexpr (D == 3) {
       const Where w = locate<D>(*desc, site);
@@ -283,6 +285,22 @@ struct Site {
           f(dx + 3 * n, iW, fma(gi, sel3(r01[dx], dy) * iz, R(-1)), sel3(f01[dx], dy) * ez, gi);
           __builtin_amdgcn_sched_barrier(0);
         }
+      }
+    } else if constexpr (REREAD) {
+      const Where w = locate<D>(*desc, site);
+#pragma unroll 1
+      for (int i = 0; i < Q; ++i) {
+        const int dx = i % 3, dy = i / 3, z = (dx == 0) + (D > 1 && dy == 0);  // zeros
+        const R W = z == D ? R(L::W(0)) : z == D - 1 ? R(L::W(1)) : R(L::W(Q / 2));
+        const T gv = *(const gptr<T>)((gaddr)(uintptr_t)src +
+                                      pidx<Q>(sel3(w.ys, dy) + sel3(w.xs, dx), i) * sizeof(T));
+        const auto pick = [&](const R(&a)[3][3]) {
+          const R q0 = sel3(a[0], dy), q1 = sel3(a[1], dy), q2 = sel3(a[2], dy);
+          return dx == 0 ? q0 : (dx == 1 ? q1 : q2);
+        };
+        const R gi = Codec<S, R>::dec(gv, W, rho_ref);
+        // (no collision is swept this way: 1/W_i is not formed)
+        f(i, R(0), fma(gi, pick(r01), R(-1)), pick(f01), gi);
       }
     } else {
       const Pass p = pass_opaque();
@@ -549,7 +567,7 @@ struct SiteDevT {
   __device__ __forceinline__ double fe_far(A seqi, double W) const {
     return double(A(W) * (r + seqi));
   }
-  template <class F>
+  template <bool REREAD = true, class F>
   __device__ __forceinline__ void sweep(const F& f) const {
     sweep_dev([&](int i, A si, A seqi, double W) {
       f(i, 0.0, x_far(si, seqi), fe_far(seqi, W), 0.0);
@@ -563,7 +581,7 @@ using SiteDev = SiteDevT<D, S, float>;
 template <class V, class R>
 __device__ __forceinline__ R S_log(const V& v, R a) {
   R s = R(0);
-  v.sweep([&](int, R, R xi, R fi, R) { s += fi * phi_log<R>((R(1) - a) * xi); });
+  v.template sweep<true>([&](int, R, R xi, R fi, R) { s += fi * phi_log<R>((R(1) - a) * xi); });
   return s;
 }
 
@@ -574,7 +592,7 @@ __device__ __forceinline__ void S_dS_log(const V& v, R a, R& Sv, R& dS, R* sA = 
   Sv = R(0);
   dS = R(0);
   R sa = R(0);
-  v.sweep([&](int, R, R xi, R fi, R) {
+  v.template sweep<true>([&](int, R, R xi, R fi, R) {
     const R y = (R(1) - a) * xi;
     const R l = dlog_clamped<R>(y);
     Sv += fi * ((y <= R(-1)) ? R(1) : (R(1) + y) * l - y);
@@ -710,13 +728,13 @@ __device__ __forceinline__ void S_dS_newton(const V& v, R a, R xabs, R& Sv, R& d
 
 // The rare path of one lane: the long series when alpha_* = 2 and
 // max|x| <= thrL, else the log1p forms.
-template <class V, class R>
+template <bool REREAD, class V, class R>
 __device__ __forceinline__ void rare_sums(const V& v, R astar, bool star2, R xabs, R& Dv, R& Ds,
                           R& Gs) {
   if (star2 && xabs <= Base<R>::thrL) {
     R sE = R(0), sO = R(0);
     const SeriesK<R, Base<R>::KL> ser;
-    v.sweep([&](int, R, R xi, R fi, R) { ser.accum(xi, fi, sE, sO); });
+    v.template sweep<REREAD>([&](int, R, R xi, R fi, R) { ser.accum(xi, fi, sE, sO); });
     R cE, cO;
     series_scale<R, Base<R>::KL>(cE, cO);
     sE *= cE;
@@ -727,7 +745,7 @@ __device__ __forceinline__ void rare_sums(const V& v, R astar, bool star2, R xab
     return;
   }
   R sD = R(0), sS = R(0), sG = R(0);
-  v.sweep([&](int, R, R xi, R fi, R) {
+  v.template sweep<REREAD>([&](int, R, R xi, R fi, R) {
     const R px = phi_log<R>(xi);
     const R py = phi_log<R>((R(1) - astar) * xi);
     sD += fi * px;
@@ -765,6 +783,7 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
   // The root solvers need alpha_max on every lane; the closed form and the
   // secant need it only where alpha_* < 2, which the tiers below detect.
   constexpr bool kXmax = (MODE == kNewton || MODE == kBisect);
+  constexpr bool kReread = V::kDim == 3 || PHASE == kPhaseAll;  // see Site::sweep
   // The closed form on 2-byte storage takes the first-term sums (and, on the
   // mixed site, forms them in FP32: sums_k1).  The root solvers keep the full
   // tiers: their root moves with D itself, by about x^2 / 12 under the
@@ -861,7 +880,7 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
     }
   } else {
     // only deferred lanes are active: max|x_i| again, and max x_i
-    v.sweep([&](int, R, R xi, R, R) {
+    v.template sweep<kReread>([&](int, R, R xi, R, R) {
       xabs = fmax(xabs, fabs(xi));
       xmax = fmax(xmax, xi);
     });
@@ -905,7 +924,7 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
     if (rare) return o;
   }
   if constexpr (PHASE == kPhaseAll && !kXmax) {
-    if (rare) v.sweep([&](int, R, R xi, R, R) { xmax = fmax(xmax, xi); });
+    if (rare) v.template sweep<kReread>([&](int, R, R xi, R, R) { xmax = fmax(xmax, xi); });
   }
   // alpha_max = min over {f^eq_i < f_i} of f_i/(f_i - f^eq_i) = 1 + 1/max_i x_i
   // (definition after Eq. (7)); alpha_* = min(2, alpha_max) (Eq. (8)), and
@@ -917,7 +936,7 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
   const R astar = star2 ? R(2) : amax;
   o.fallback = rare;
   if (__any(rare)) {
-    if (rare) rare_sums(v, astar, star2, xabs, Dv, Ds, Gs);
+    if (rare) rare_sums<kReread>(v, astar, star2, xabs, Dv, Ds, Gs);
   }
   // f = f^eq to rounding: the paper leaves alpha free there; take alpha_*.
   const bool guard = !has_pos || !(Dv > Prec<R>::guard * v.rho);
@@ -1910,45 +1929,26 @@ constexpr int step_waves() {
   return 1;
 }
 
-template <int D, class S, int MODE, class R, bool SUMS>
+template <int D, class S, int MODE, class R, bool SUMS, int ELBM_TILES>
 __global__ void __launch_bounds__(kBlock, (step_waves<S, MODE>())) k_step(const BatchArgs args) {
   using T = typename S::T;
   constexpr int Q = Lattice<D>::Q;
-  constexpr int ELBM_TILES = tiles_per_block(sizeof(T), Q);
+  constexpr int kSplit = tiles_per_block(sizeof(T), Q) / ELBM_TILES;  // workgroups per described one
   const int b = blockIdx.x;
   int si = 0;
   for (int k = 1; k < args.n; ++k)
-    if (b >= args.d[k].block_begin) si = k;
+    if (b >= args.d[k].block_begin * kSplit) si = k;
   const SimDesc& d = args.d[si];
   const T* __restrict__ src = static_cast<const T*>(d.src);
   T* __restrict__ dst = static_cast<T*>(d.dst);
   const int diag = d.diag;
   const uint32_t N = (uint32_t)d.nx * (uint32_t)d.ny * (uint32_t)d.nz;
-  const uint32_t lb = (uint32_t)(b - d.block_begin);
-  const uint32_t chunk = (uint32_t)d.nblocks >> 3;
+  const uint32_t lb = (uint32_t)(b - d.block_begin * kSplit);
+  const uint32_t chunk = ((uint32_t)d.nblocks >> 3) * kSplit;
   const uint32_t unit = (lb & 7u) * chunk + (lb >> 3);  // this workgroup's tile group
   Acc acc;
   acc.init();
-  constexpr bool kRoot = MODE == kNewton || MODE == kBisect || MODE == kSecant;
-  if (unit * ELBM_TILES * kBlock >= N) {
-    if (!(diag & kDiagCounts)) return;  // padding workgroup
-  } else if constexpr (kRoot) {
-    // The root solvers are bound by their arithmetic: tile after tile in a
-    // rolled loop, one copy of the solver's passes in the instruction cache
-    // and one tile's populations in registers.
-#pragma unroll 1
-    for (int k = 0; k < ELBM_TILES; ++k) {
-      uint32_t flags = 0;
-      if ((unit * ELBM_TILES + k) * kBlock < N) {
-        const uint32_t s = (unit * ELBM_TILES + k) * kBlock + threadIdx.x;
-        Slot<T> raw[Q];
-        if (d.nx % 64 == 0) load_site_row<D>(d, src, s < N ? s : 0u, raw);
-        else load_site<D>(d, src, s < N ? s : 0u, raw);
-        flags = site_update<D, S, MODE, R, SUMS>(d, src, dst, s, s < N, raw, acc, diag).flags;
-      }
-      if (diag & kDiagCounts) acc.count_flags(flags);
-    }
-  } else {
+  if (unit * ELBM_TILES * kBlock < N) {
     Slot<T> raw[ELBM_TILES][Q];
 #if ELBM_LOAD_PRIO
     __builtin_amdgcn_s_setprio(ELBM_LOAD_PRIO);
@@ -2027,21 +2027,44 @@ __global__ void __launch_bounds__(kBlock, (step_waves<S, MODE>())) k_step(const 
       }
       if (ELBM_TILES == 1 && (diag & kDiagCounts)) acc.count_flags(flags);
     }
+  } else if (!(diag & kDiagCounts)) {
+    return;  // padding workgroup
   }
-  if (diag & kDiagCounts) store_records<kRoot>(acc, d, (int)lb);
+  if (diag & kDiagCounts)
+    store_records<MODE == kNewton || MODE == kBisect || MODE == kSecant>(acc, d, (int)lb);
 }
 
 // The sums of ELBM_DIAG_SUMS (which need logarithms per site) are compiled
 // into a kernel of their own, used when a simulation of the batch asks for
 // them, so that the other kernels do not carry their registers.
+//
+// A launch of few workgroups takes one tile per workgroup instead of four:
+// four tiles keep more bytes in flight per wavefront where the chip is full,
+// but below a few workgroups per CU they leave CUs idle or a last round
+// nearly empty, and a wavefront's four updates run one after another.  The
+// line lies where the two cross, in described (four-tile) workgroups, measured
+// on shear layers (us per step, four tiles / one): FP32 256^2 7.5 / 4.0,
+// 1001 x 601 (588 workgroups) 14.3 / 11.4, 1024^2 (1024) 18.7 / 19.1, 4096^2
+// 231 / 242; FP16 with FP64 arithmetic 1500^2 (2200) 29.9 / 28.5, 2048^2 (4096)
+// 48.2 / 50.9; LBGK in FP32 1001 x 601 11.8 / 10.2, 1024^2 14.5 / 19.2; Newton
+// in FP32 64^2 18.0 / 6.5, 1001 x 601 28.3 / 22.9, 4096^2 447 / 480.
+// Launches that record counts keep four (one record per described workgroup).
+constexpr int one_tile_grid(int elem_bytes) { return elem_bytes == 2 ? 2304 : 768; }
 template <int D, class S, int MODE, class R>
 hipError_t launch_step(const BatchArgs& a, int grid, hipStream_t st) {
-  bool sums = false;
-  for (int k = 0; k < a.n; ++k) sums = sums || (a.d[k].diag & kDiagSums);
-  if (sums)
-    k_step<D, S, MODE, R, true><<<grid, kBlock, 0, st>>>(a);
+  constexpr int kTiles = tiles_per_block(sizeof(typename S::T), Lattice<D>::Q);
+  int diag = 0;
+  for (int k = 0; k < a.n; ++k) diag |= a.d[k].diag;
+  if constexpr (kTiles > 1) {
+    if (!(diag & kDiagCounts) && grid <= one_tile_grid(sizeof(typename S::T))) {
+      k_step<D, S, MODE, R, false, 1><<<grid * kTiles, kBlock, 0, st>>>(a);
+      return hipGetLastError();
+    }
+  }
+  if (diag & kDiagSums)
+    k_step<D, S, MODE, R, true, kTiles><<<grid, kBlock, 0, st>>>(a);
   else
-    k_step<D, S, MODE, R, false><<<grid, kBlock, 0, st>>>(a);
+    k_step<D, S, MODE, R, false, kTiles><<<grid, kBlock, 0, st>>>(a);
   return hipGetLastError();
 }
 

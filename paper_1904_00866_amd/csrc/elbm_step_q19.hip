@@ -181,7 +181,7 @@ struct SiteQ19 {
   __device__ __forceinline__ R fsel(int dx, int dy, int dz) const {
     return dz == 0 ? sel9(F0, dx, dy) : sel9(F1, dx, dy) * sel3(e2, dz);
   }
-  template <class F>
+  template <bool REREAD = true, class F>
   __device__ __forceinline__ void sweep(const F& f) const {
     const Where w = locate<3>(*desc, site);
 #pragma unroll 1
