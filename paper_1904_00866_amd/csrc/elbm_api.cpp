@@ -226,6 +226,7 @@ struct elbm_sim {
   int64_t t;
   bool have_alpha, have_stats;
   StepLauncher launch;
+  FusedLauncher fused;  // nullptr: single steps only
 };
 
 namespace {
@@ -278,12 +279,123 @@ SimDesc desc_of(const elbm_sim* s, int block_begin, bool last) {
   return d;
 }
 
-// last: as for desc_of (a step that records nothing leaves nothing to read)
-void after_step(elbm_sim* s, bool last) {
+// last: as for desc_of (a step that records nothing leaves nothing to read);
+// nsub: the steps the launch took
+void after_step(elbm_sim* s, bool last, int nsub = 1) {
   s->cur = 1 - s->cur;
-  s->t += 1;
+  s->t += nsub;
   s->have_alpha = last && (s->cfg.diag & ELBM_DIAG_ALPHA);
   s->have_stats = last && (s->cfg.diag & ELBM_DIAG_COUNTS);
+}
+
+// How launches run: nsub steps fused (1: a single step) on regions of
+// geometry geom, `launches` times.  After n steps the state lies in the buffer
+// where n single steps leave it (a captured call of an even number of steps
+// can be replayed): an even nsub is launched twice.
+struct Fusion {
+  int nsub = 1, geom = kFused16x16;
+  int launches() const { return nsub % 2 ? 1 : 2; }
+  int64_t steps() const { return int64_t(nsub) * launches(); }
+};
+
+// Tiles of a simulation under f.
+int64_t fused_tiles(const elbm_sim* s, const Fusion& f) {
+  const int64_t ix = kFusedX[f.geom] - 2 * (f.nsub - 1), iy = kFusedY[f.geom] - 2 * (f.nsub - 1);
+  return ((s->cfg.nx + ix - 1) / ix) * ((s->cfg.ny + iy - 1) / iy);
+}
+
+// The fusion of boxes beyond the small ones, by what bounds a single step of
+// the type there: the line between its FP64 arithmetic and its memory traffic
+// (us per step single / fused, 1001 x 601, 1024^2, 2048^2, 4096^2 unless
+// noted; fusing costs the frames' arithmetic).
+Fusion large_fusion(const elbm_config& c, int64_t sites) {
+  const bool bgk = c.alpha_mode == ELBM_ALPHA_BGK;
+  const Fusion no, two16{2, kFused16x16}, two32{2, kFused32x32}, three32{3, kFused32x32},
+      two64{2, kFused64x16};
+  constexpr int64_t k400 = 400000, M = 1 << 20;
+  switch (c.storage) {
+    case ELBM_STORE_F64:  // memory-bound: LBGK 17.8/7.3 29.7/10.2 106/45 416/171,
+      // closed form 18.3/11.8 29.4/19.5 104/82 408/321
+      return bgk ? three32 : two16;
+    case ELBM_STORE_F32:
+      // LBGK 9.8/6.2 14.6/8.5 57/30 214/117
+      if (bgk) return three32;
+      // FP32 arithmetic (at most two: three gains nothing) 10.2/7.8 15.0/11.4 57/39 214/151
+      if (c.alpha_fp64 == ELBM_ARITH_FP32) return two32;
+      // mixed: 512^2 5.8/5.3 on 16 x 16; 10.7/9.7 16.3/13.9 58/49 210/187 on 64 x 16
+      if (c.alpha_fp64 == ELBM_ARITH_MIXED) return sites < k400 ? two16 : two64;
+      // FP64 arithmetic: 512^2 none, 10.8/10.5 18.0/15.5 61/57 221/221
+      return sites > 3 * M / 4 && sites < 8 * M ? two32 : no;
+    case ELBM_STORE_F32_DEV:
+      // mixed as for F32; FP64 arithmetic 11.3/12.1 19.3/19.1 65/71 239/272: none
+      if (c.alpha_fp64 == ELBM_ARITH_MIXED) return sites < k400 ? two16 : two64;
+      return bgk ? three32 : no;
+    default:
+      // FP16: LBGK 7.2/6.5 9.7/9.8 39/33 138/129; mixed 512^2 4.7/4.1, 9.7/10.2
+      // (1024^2) 37/32 120/119; FP64 arithmetic 9.0/8.9 12.3/13.4 46/46 169/179: none
+      if (bgk) return sites > 2 * M ? two32 : no;
+      if (c.alpha_fp64 != ELBM_ARITH_MIXED) return no;
+      return sites < k400 ? two16 : sites > 2 * M && sites < 12 * M ? two64 : no;
+  }
+}
+
+// The fusion of a launch over n simulations that may take up to `free` steps
+// without recording.  Small boxes (16 x 16 regions): as many steps as leave
+// one workgroup per CU, up to six, since a launch then costs its latency only
+// (100^2 FP32, us per step: single 4.9, five steps on 169 workgroups 1.7, six on
+// 289 2.3); three where that is at most four rounds of workgroups (256^2 3.9 /
+// 2.8, 360^2 4.8 / 3.7, 512^2 6.0 / 6.2).
+Fusion fusion_of(elbm_sim* const* sims, size_t n, int64_t free) {
+  Fusion f;
+  if (free < 2 || !sims[0]->fused) return f;
+  int64_t sites = 0;
+  for (size_t k = 0; k < n; ++k) {  // 32-bit byte offsets into a buffer
+    if (elbm_checkpoint_bytes(sims[k]) > UINT32_MAX) return f;
+    sites += sims[k]->L.N;
+  }
+  constexpr int kMost = 6, kCUs = 256, kRounds = 4;
+  const auto tiles = [&](int nsub) {
+    int64_t t = 0;
+    for (size_t k = 0; k < n; ++k) t += fused_tiles(sims[k], Fusion{nsub, kFused16x16});
+    return t;
+  };
+  if (tiles(3) <= kRounds * kCUs) {
+    f.nsub = kMost;
+    while (f.nsub > 3 && tiles(f.nsub) > kCUs) --f.nsub;
+  } else {
+    f = large_fusion(sims[0]->cfg, sites);
+  }
+  while (f.nsub > 1 && f.steps() > free) --f.nsub;
+  if (f.nsub == 1) f.geom = kFused16x16;
+  return f;
+}
+
+// Advance each of the n simulations by f.steps() steps.  last: per simulation,
+// whether they end its call.
+hipError_t launch_steps(elbm_sim* const* sims, const char* last, size_t n, const Fusion& f) {
+  for (int r = 0; r < f.launches(); ++r) {
+    BatchArgs a;
+    a.n = 0;
+    int blocks = 0;
+    for (size_t k = 0; k < n; ++k) {
+      SimDesc& d = a.d[a.n++];
+      d = desc_of(sims[k], blocks, last[k] && f.nsub == 1);
+      // (a multiple of 8 workgroups for the XCD-aware order)
+      if (f.nsub > 1) d.nblocks = int((fused_tiles(sims[k], f) + 7) / 8 * 8);
+      blocks += d.nblocks;
+    }
+    const elbm_sim* s0 = sims[0];
+    const hipError_t e = f.nsub > 1 ? s0->fused(a, blocks, f.nsub, f.geom, s0->stream)
+                                    : s0->launch(a, blocks, s0->stream);
+    if (e != hipSuccess) return e;
+    for (size_t k = 0; k < n; ++k) after_step(sims[k], last[k], f.nsub);
+  }
+  return hipSuccess;
+}
+
+// Steps of a call with `left` to go that need not record anything.
+int64_t free_steps(const elbm_sim* s, int64_t left) {
+  return s->cfg.diag & (ELBM_DIAG_ALPHA | ELBM_DIAG_COUNTS | ELBM_DIAG_SUMS) ? left - 1 : left;
 }
 
 elbm_status check_sim(const elbm_sim* s) {
@@ -378,6 +490,8 @@ elbm_sim* new_handle(const elbm_config* cfg, const Layout& L, void* dev_state, v
   s->t = 0;
   s->have_alpha = s->have_stats = false;
   s->launch = step_launcher(cfg->lattice, cfg->storage, cfg->alpha_mode, cfg->alpha_fp64,
+                            cfg->entropy);
+  s->fused = fused_launcher(cfg->lattice, cfg->storage, cfg->alpha_mode, cfg->alpha_fp64,
                             cfg->entropy);
   return s;
 }
@@ -510,13 +624,12 @@ elbm_status elbm_step(elbm_sim* s, int64_t nsteps) {
   if (nsteps < 0) return fail(ELBM_EINVAL, "nsteps < 0");
   DeviceGuard g(s->device);
   if (!g.ok) return fail(ELBM_EDEVICE, "cannot select the simulation's device");
-  BatchArgs a;
-  a.n = 1;
-  for (int64_t k = 0; k < nsteps; ++k) {
-    a.d[0] = desc_of(s, 0, k == nsteps - 1);
-    hipError_t e = s->launch(a, s->L.nblocks, s->stream);
+  for (int64_t left = nsteps; left > 0;) {
+    const Fusion f = fusion_of(&s, 1, free_steps(s, left));
+    const char last = left == f.steps();
+    const hipError_t e = launch_steps(&s, &last, 1, f);
     if (e != hipSuccess) return hip_fail(e, "step kernel launch");
-    after_step(s, k == nsteps - 1);
+    left -= f.steps();
   }
   return ELBM_OK;
 }
@@ -546,27 +659,24 @@ elbm_status elbm_step_batch(elbm_sim* const* sims, const int64_t* nsteps, int32_
   std::vector<char> last;  // this step is the simulation's last of the call
   active.reserve(size_t(n));
   last.reserve(size_t(n));
-  for (int64_t step = 0; step < kmax; ++step) {
+  for (int64_t step = 0; step < kmax;) {
     active.clear();
-    last.clear();
+    int64_t free = kmax;
     for (int32_t k = 0; k < n; ++k)
       if (nsteps[k] > step) {
         active.push_back(sims[k]);
-        last.push_back(nsteps[k] == step + 1);
+        free = std::min(free, free_steps(sims[k], nsteps[k] - step));
       }
+    const Fusion f = fusion_of(active.data(), active.size(), free);
+    last.clear();
+    for (int32_t k = 0; k < n; ++k)
+      if (nsteps[k] > step) last.push_back(nsteps[k] == step + f.steps());
     for (size_t c0 = 0; c0 < active.size(); c0 += kMaxBatch) {
-      BatchArgs a;
-      a.n = 0;
-      int blocks = 0;
-      const size_t c1 = std::min(active.size(), c0 + size_t(kMaxBatch));
-      for (size_t k = c0; k < c1; ++k) {
-        a.d[a.n++] = desc_of(active[k], blocks, last[k]);
-        blocks += active[k]->L.nblocks;
-      }
-      hipError_t e = s0->launch(a, blocks, s0->stream);
+      const size_t c = std::min(active.size() - c0, size_t(kMaxBatch));
+      const hipError_t e = launch_steps(active.data() + c0, last.data() + c0, c, f);
       if (e != hipSuccess) return hip_fail(e, "batched step kernel launch");
-      for (size_t k = c0; k < c1; ++k) after_step(active[k], last[k]);
     }
+    step += f.steps();
   }
   return ELBM_OK;
 }
@@ -592,18 +702,21 @@ elbm_status elbm_step_noalloc(elbm_sim* s, int64_t nsteps, uint32_t diag,
   if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
   char* counts = static_cast<char*>(p);
   char* sums = (diag & ELBM_DIAG_SUMS) ? counts + kScratchCountBytes : nullptr;
+  const char no = 0;
+  for (int64_t left = nsteps - 1; left > 0;) {
+    const Fusion f = fusion_of(&s, 1, left);
+    if ((e = launch_steps(&s, &no, 1, f)) != hipSuccess) return hip_fail(e, "step kernel launch");
+    left -= f.steps();
+  }
   BatchArgs a;
   a.n = 1;
-  for (int64_t k = 0; k < nsteps; ++k) {
-    const bool last = k == nsteps - 1;
-    a.d[0] = desc_of(s, 0, last);
-    a.d[0].counts = counts;
-    a.d[0].sums = sums;
-    a.d[0].diag = last ? int((s->cfg.diag & ELBM_DIAG_ALPHA) | diag) : 0;
-    if ((e = s->launch(a, s->L.nblocks, s->stream)) != hipSuccess)
-      return hip_fail(e, "step kernel launch");
-    after_step(s, last);
-  }
+  a.d[0] = desc_of(s, 0, true);
+  a.d[0].counts = counts;
+  a.d[0].sums = sums;
+  a.d[0].diag = int((s->cfg.diag & ELBM_DIAG_ALPHA) | diag);
+  if ((e = s->launch(a, s->L.nblocks, s->stream)) != hipSuccess)
+    return hip_fail(e, "step kernel launch");
+  after_step(s, true);
   // the handle's own records were not written by these steps
   s->have_stats = false;
   if ((e = launch_reduce(counts, sums, s->L.nblocks,

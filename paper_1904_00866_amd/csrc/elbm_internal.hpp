@@ -113,6 +113,15 @@ StepLauncher step_launcher_d3(int storage, int mode, int fp64);
 StepLauncher step_launcher_q19(int storage, int mode, int fp64);
 StepLauncher step_launcher_burg(int lattice, int storage, int mode, int fp64);
 
+// Several steps of a D2Q9 box in one launch (elbm_step_fused.hip): nsub steps
+// of every simulation of the batch, each workgroup on a region of geometry
+// geom, whose buffers hold less than 4 GiB.
+enum { kFused16x16 = 0, kFused32x32, kFused64x16 };
+constexpr int kFusedX[] = {16, 32, 64}, kFusedY[] = {16, 32, 16};
+using FusedLauncher = hipError_t (*)(const BatchArgs&, int grid, int nsub, int geom, hipStream_t);
+// nullptr where the lattice, mode or arithmetic has none
+FusedLauncher fused_launcher(int lattice, int storage, int mode, int fp64, int entropy);
+
 // Auxiliary kernels: a population buffer `buf` in the layout of pidx().
 struct BoxDesc {
   int lattice, D, storage;

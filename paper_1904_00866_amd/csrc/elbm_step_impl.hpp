@@ -150,6 +150,7 @@ struct Site {
   static constexpr int kDim = D;
   // f^eq_i = f01[dx][dy] e2[dz]: the common tier sums over c_z per (c_x, c_y)
   static constexpr bool kZFactor = (D == 3);
+  static constexpr bool kReread = (D == 3);  // sweep() re-reads the populations
   static constexpr bool kSumsK1 = false;
   typename Kept<S>::type raw[Q];  // the loaded populations as kept (Kept<S>)
   R rho, irho, rho_ref;
@@ -261,7 +262,7 @@ struct Site {
   // wavefront has just filled.  So do the root solvers' passes on any lattice
   // (REREAD), one direction at a time: their four unrolled tiles hold one
   // body of the logarithms each, more would keep the tiles from unrolling.
-  template <bool REREAD = (D == 3), class F>
+  template <bool REREAD = kReread, class F>
   __device__ __forceinline__ void sweep(const F& f) const {
     if constexpr (D == 3) {
       const Where w = locate<D>(*desc, site);
@@ -367,6 +368,8 @@ struct SiteDevT {
   static constexpr int Q = L::Q;
   static constexpr int kDim = D;
   static constexpr bool kZFactor = false;  // f^eq_i comes from s^eq_i
+  // sweep() re-reads the populations
+  static constexpr bool kReread = D == 3 || (D == 2 && sizeof(T) == 2);
   static constexpr bool kSumsK1 = true;     // sums_k1() below
   // the collision takes s_i - s^eq_i as sums_k1 formed them where that costs
   // fewer registers than the factors s^eq_i is recomputed from
@@ -513,9 +516,9 @@ struct SiteDevT {
   // the collision that follows it (see Site::sweep), and the values x_i and
   // f^eq_i of a direction as the rare tier forms them: through the reciprocal
   // of rho_ref + s^eq_i itself, not the per-axis factors.
-  template <class F>
+  template <bool REREAD = kReread, class F>
   __device__ __forceinline__ void sweep_dev(const F& f) const {
-    if constexpr (D == 2 && sizeof(T) == 2) {
+    if constexpr (D == 2 && REREAD) {
       // one direction at a time: with more in flight this kernel loses the
       // six waves per SIMD that its common path runs at (78 VGPRs), 4 % of
       // its time at 4096^2
@@ -567,9 +570,9 @@ struct SiteDevT {
   __device__ __forceinline__ double fe_far(A seqi, double W) const {
     return double(A(W) * (r + seqi));
   }
-  template <bool REREAD = true, class F>
+  template <bool REREAD = kReread, class F>
   __device__ __forceinline__ void sweep(const F& f) const {
-    sweep_dev([&](int i, A si, A seqi, double W) {
+    sweep_dev<REREAD>([&](int i, A si, A seqi, double W) {
       f(i, 0.0, x_far(si, seqi), fe_far(seqi, W), 0.0);
     });
   }
@@ -770,7 +773,10 @@ struct AlphaOut {
 // kPhaseRare then handles only those lanes, after the common phase's values
 // have died, so the long series and the logarithms do not raise the
 // register peak of the common path.
-enum { kPhaseAll = 0, kPhaseCommon = 1, kPhaseRare = 2 };
+// kPhaseRareReg is kPhaseRare for a site whose populations are not in memory
+// (a step fused with the one before it): every pass runs on the registers.
+enum { kPhaseAll = 0, kPhaseCommon = 1, kPhaseRare = 2, kPhaseRareReg = 3 };
+constexpr bool is_rare_phase(int phase) { return phase >= kPhaseRare; }
 
 // The choice of alpha at one site (all lanes of the wavefront call it).
 // V: the site type (lattice, storage, arithmetic).
@@ -783,7 +789,8 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
   // The root solvers need alpha_max on every lane; the closed form and the
   // secant need it only where alpha_* < 2, which the tiers below detect.
   constexpr bool kXmax = (MODE == kNewton || MODE == kBisect);
-  constexpr bool kReread = V::kDim == 3 || PHASE == kPhaseAll;  // see Site::sweep
+  // see Site::sweep
+  constexpr bool kReread = PHASE == kPhaseAll || (PHASE != kPhaseRareReg && V::kReread);
   // The closed form on 2-byte storage takes the first-term sums (and, on the
   // mixed site, forms them in FP32: sums_k1).  The root solvers keep the full
   // tiers: their root moves with D itself, by about x^2 / 12 under the
@@ -833,13 +840,13 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
   constexpr int KC = kS16 ? 1 : Base<R>::K;
   const R thrC = kS16 ? Base<R>::thrM : Base<R>::thr;
   R xmax = R(-1), xabs = R(0), sE = R(0), sO = R(0);
-  if constexpr (PHASE != kPhaseRare && kK1) {
+  if constexpr (!is_rare_phase(PHASE) && kK1) {
     typename V::Arith E, O, xm;
     v.sums_k1(v.pass(), E, O, xm);
     sE = E;
     sO = O;
     xabs = xm;
-  } else if constexpr (PHASE != kPhaseRare) {
+  } else if constexpr (!is_rare_phase(PHASE)) {
   const SeriesK<R, KC> ser;
   const auto P = v.pass();
   if constexpr (V::kZFactor) {
@@ -871,7 +878,7 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
     }
   }
   }
-  if constexpr (PHASE != kPhaseRare) {
+  if constexpr (!is_rare_phase(PHASE)) {
     if constexpr (!kK1) {
       R cE, cO;
       series_scale<R, KC>(cE, cO);
@@ -892,9 +899,9 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
   // rare phase was deferred by the common phase and stays rare: max|x_i|
   // formed again by another sequence may round differently and must not
   // send it back to a tier whose sums it has not formed.
-  const bool common = PHASE != kPhaseRare && xabs <= thrC;
-  const bool mid = PHASE != kPhaseRare && !common && xabs <= Base<R>::thrM;
-  const bool rare = PHASE == kPhaseRare || !(xabs <= Base<R>::thrM);
+  const bool common = !is_rare_phase(PHASE) && xabs <= thrC;
+  const bool mid = !is_rare_phase(PHASE) && !common && xabs <= Base<R>::thrM;
+  const bool rare = is_rare_phase(PHASE) || !(xabs <= Base<R>::thrM);
   if constexpr (PHASE == kPhaseCommon) {
     if (rare) {
       o.deferred = true;
@@ -904,7 +911,7 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
       o.iters = 0;
     }
   }
-  if (PHASE != kPhaseRare && __any(mid)) {
+  if (!is_rare_phase(PHASE) && __any(mid)) {
     R mE = R(0), mO = R(0);
     const SeriesK<R, Base<R>::KM> ser;
     const auto P = v.pass_opaque();
@@ -968,7 +975,7 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
         // |(1 - a) x_i| <= |x_i|); otherwise from Newton's passes (series
         // where every lane's |(1 - a) x_i| allows it, else log1p).
         constexpr int KS = Base<R>::K, NP = 2 * KS + 2;
-        const bool poly = PHASE != kPhaseRare && d.secant_iters > 2 && __all(common);
+        const bool poly = !is_rare_phase(PHASE) && d.secant_iters > 2 && __all(common);
         R M[NP];
 #pragma unroll
         for (int n = 0; n < NP; ++n) M[n] = R(0);
@@ -1649,20 +1656,38 @@ __device__ __forceinline__ uint32_t record_site(const SimDesc& d, uint32_t s, bo
   return flags;
 }
 
+// Where a site's new populations go: its place in a buffer's block.  begin()
+// forms the addresses, where the stores begin.
+template <int Q, class T>
+struct ToBlock {
+  T* dst;
+  uint32_t s;
+  uint32_t lo;
+  gaddr blk;
+  __device__ __forceinline__ ToBlock(T* dst_, uint32_t s_) : dst(dst_), s(s_) {}
+  __device__ __forceinline__ void begin() {
+    lo = (s & 63u) * (uint32_t)sizeof(T);
+    blk = block_base<Q>(dst, s);
+  }
+  __device__ __forceinline__ void operator()(int i, T v) const {
+    constexpr uint32_t es = sizeof(T);
+    st_nt<T>(blk + (uint64_t)i * (kLane * es), kLane * es, lo, v);
+  }
+};
+
 // The site update on the deviations (SiteDevT) in the arithmetic A: FP32
 // (the mixed policy, every mode; the entropy differences and alpha in
 // FP64), or FP64 (the closed form's common phase on FP16 deviation storage).
-template <int D, class S, class A, int MODE, bool SUMS, int PHASE>
+template <int D, class S, class A, int MODE, bool SUMS, int PHASE, class Out>
 __device__ __forceinline__ SiteOut site_update_dev(const SimDesc& d,
                                                 const typename S::T* __restrict__ src,
-                                                typename S::T* __restrict__ dst, uint32_t s,
+                                                Out& out, uint32_t s,
                                                 bool live,
                                                 const Slot<typename S::T> (&raw)[Lattice<D>::Q],
                                                 Acc& acc, int diag) {
   using L = Lattice<D>;
   constexpr int Q = L::Q;
   using T = typename S::T;
-  constexpr uint32_t es = sizeof(T);
   const uint32_t sl = live ? s : 0u;
   SiteDevT<D, S, A> v;
 #pragma unroll
@@ -1674,8 +1699,7 @@ __device__ __forceinline__ SiteOut site_update_dev(const SimDesc& d,
   const A ab = A(ao.alpha * d.beta);
   const auto P = v.pass_opaque();
   A tmin = A(INFINITY);  // min of f~_i / W_i: its sign is that of f~_i
-  const uint32_t lo = (s & 63u) * es;
-  const gaddr blk = block_base<Q>(dst, s);
+  out.begin();
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     const A si = v.s(i);
@@ -1684,23 +1708,22 @@ __device__ __forceinline__ SiteOut site_update_dev(const SimDesc& d,
     constexpr bool kDD = sizeof(T) == 2 && MODE == kClosed && PHASE == kPhaseCommon;
     const A sn = kDD ? fma(-ab, v.dev(i, P), si) : fma(ab, v.seq(i, P) - si, si);
     if constexpr (PHASE != kPhaseCommon) tmin = fmin(tmin, v.r + sn);
-    st_nt<T>(blk + i * kLane * es, kLane * es, lo, v.enc(i, sn));
+    out(i, v.enc(i, sn));
     sched_group(i);
   }
   return SiteOut{false, record_site<SUMS>(d, s, live, v, ao, double(tmin), j, acc, diag)};
 }
 
 // The site update in FP64 or FP32 site arithmetic (R), every alpha mode.
-template <int D, class S, int MODE, class R, bool SUMS, int PHASE>
+template <int D, class S, int MODE, class R, bool SUMS, int PHASE, class Out>
 __device__ __forceinline__ SiteOut site_update_fp(const SimDesc& d,
                                                const typename S::T* __restrict__ src,
-                                               typename S::T* __restrict__ dst, uint32_t s,
+                                               Out& out, uint32_t s,
                                                bool live, const Slot<typename S::T> (&raw)[Lattice<D>::Q],
                                                Acc& acc, int diag) {
   using L = Lattice<D>;
   constexpr int Q = L::Q;
   using T = typename S::T;
-  constexpr uint32_t es = sizeof(T);
   const uint32_t sl = live ? s : 0u;  // the site whose values were loaded
 
   Site<D, S, R> v;
@@ -1717,8 +1740,7 @@ __device__ __forceinline__ SiteOut site_update_fp(const SimDesc& d,
     const R tb = R(2) * beta;
     R ftmin = R(INFINITY);
     uint32_t flags = 0;
-    const uint32_t lo = (s & 63u) * es;
-    const gaddr blk = block_base<Q>(dst, s);
+    out.begin();
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       const R cu = R(L::c(i, 0)) * u[0] + R(L::c(i, 1)) * u[1] + R(L::c(i, 2)) * u[2];
@@ -1726,7 +1748,7 @@ __device__ __forceinline__ SiteOut site_update_fp(const SimDesc& d,
       const R gi = v.g(i);
       const R ft = gi + tb * (fe - gi);
       ftmin = fmin(ftmin, ft);
-      st_nt<T>(blk + i * kLane * es, kLane * es, lo, Codec<S, R>::enc(ft, R(L::invW(i)), v.rho_ref));
+      out(i, Codec<S, R>::enc(ft, R(L::invW(i)), v.rho_ref));
     }
     if (diag & kDiagCounts) {
       if (live)
@@ -1753,8 +1775,7 @@ __device__ __forceinline__ SiteOut site_update_fp(const SimDesc& d,
     const R ab = ao.alpha * beta;
     const auto P = v.pass();
     R ftmin = R(INFINITY);
-    const uint32_t lo = (s & 63u) * es;
-    const gaddr blk = block_base<Q>(dst, s);
+    out.begin();
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       const R gi = v.g(i);
@@ -1763,7 +1784,7 @@ __device__ __forceinline__ SiteOut site_update_fp(const SimDesc& d,
       // so f~_i = f^eq_i (1 + (1 - alpha beta) x_i) > 0.975 f^eq_i: no
       // negative population to look for.
       if constexpr (PHASE != kPhaseCommon) ftmin = fmin(ftmin, ft);
-      st_nt<T>(blk + i * kLane * es, kLane * es, lo, Codec<S, R>::enc(ft, R(L::invW(i)), v.rho_ref));
+      out(i, Codec<S, R>::enc(ft, R(L::invW(i)), v.rho_ref));
       sched_group(i);
     }
     return SiteOut{false, record_site<SUMS>(d, s, live, v, ao, ftmin, j, acc, diag)};
@@ -1780,9 +1801,9 @@ __device__ __forceinline__ SiteOut site_update_fp(const SimDesc& d,
 // PHASE (closed form): kPhaseCommon leaves the lanes that need the rare
 // tier untouched and returns true for them; site_update_rare completes them.
 // AP: the arithmetic policy (double, float or Mixed).
-template <int D, class S, int MODE, class AP, bool SUMS, int PHASE = kPhaseAll>
+template <int D, class S, int MODE, class AP, bool SUMS, int PHASE = kPhaseAll, class Out>
 __device__ __forceinline__ SiteOut site_update(const SimDesc& d, const typename S::T* __restrict__ src,
-                                            typename S::T* __restrict__ dst, uint32_t s,
+                                            Out& out, uint32_t s,
                                             bool live, const Slot<typename S::T> (&raw)[Lattice<D>::Q],
                                             Acc& acc, int diag) {
   // the closed form's common phase on FP16 deviations with FP64 site
@@ -1792,11 +1813,11 @@ __device__ __forceinline__ SiteOut site_update(const SimDesc& d, const typename 
   constexpr bool kDev64 = std::is_same<AP, double>::value && Codec<S, double>::kF16 &&
                           MODE == kClosed && PHASE == kPhaseCommon && Lattice<D>::Q <= 9;
   if constexpr (kIsMixed<AP>)
-    return site_update_dev<D, S, float, MODE, SUMS, PHASE>(d, src, dst, s, live, raw, acc, diag);
+    return site_update_dev<D, S, float, MODE, SUMS, PHASE>(d, src, out, s, live, raw, acc, diag);
   else if constexpr (kDev64)
-    return site_update_dev<D, S, double, MODE, SUMS, PHASE>(d, src, dst, s, live, raw, acc, diag);
+    return site_update_dev<D, S, double, MODE, SUMS, PHASE>(d, src, out, s, live, raw, acc, diag);
   else
-    return site_update_fp<D, S, MODE, AP, SUMS, PHASE>(d, src, dst, s, live, raw, acc, diag);
+    return site_update_fp<D, S, MODE, AP, SUMS, PHASE>(d, src, out, s, live, raw, acc, diag);
 }
 
 // The rare path of the mixed policy (SiteDev).
@@ -1991,7 +2012,8 @@ __global__ void __launch_bounds__(kBlock, (step_waves<S, MODE>())) k_step(const 
         const uint32_t s = (unit * ELBM_TILES + k) * kBlock + threadIdx.x;
         deferred[k] = false;
         if (k == 0 || (unit * ELBM_TILES + k) * kBlock < N) {
-          const SiteOut o = site_update<D, S, MODE, R, SUMS, kPhaseCommon>(d, src, dst, s, s < N,
+          ToBlock<Q, T> out(dst, s);
+          const SiteOut o = site_update<D, S, MODE, R, SUMS, kPhaseCommon>(d, src, out, s, s < N,
                                                                            raw[k], acc, diag);
           deferred[k] = o.deferred;
           flags = o.flags;
@@ -2018,8 +2040,10 @@ __global__ void __launch_bounds__(kBlock, (step_waves<S, MODE>())) k_step(const 
 #pragma unroll
       for (int k = 0; k < ELBM_TILES; ++k) {
         const uint32_t s = (unit * ELBM_TILES + k) * kBlock + threadIdx.x;
-        if (k == 0 || (unit * ELBM_TILES + k) * kBlock < N)
-          flags = site_update<D, S, MODE, R, SUMS>(d, src, dst, s, s < N, raw[k], acc, diag).flags;
+        if (k == 0 || (unit * ELBM_TILES + k) * kBlock < N) {
+          ToBlock<Q, T> out(dst, s);
+          flags = site_update<D, S, MODE, R, SUMS>(d, src, out, s, s < N, raw[k], acc, diag).flags;
+        }
         if (ELBM_TILES > 1 && (diag & kDiagCounts)) {
           acc.count_flags(flags);
           flags = 0;

@@ -46,6 +46,7 @@ struct SiteQ19 {
   static constexpr int Q = 19;
   static constexpr int kDim = 3;
   static constexpr bool kZFactor = false;
+  static constexpr bool kReread = true;  // sweep() re-reads the populations
   // FP16 deviation storage with FP64 arithmetic: the closed form's common
   // tier takes its first-term sums from the deviations (sums_k1)
   static constexpr bool kSumsK1 =
