@@ -760,6 +760,65 @@ __device__ __forceinline__ void rare_sums(const V& v, R astar, bool star2, R xab
   Gs = sG;
 }
 
+// The power sums M_n = sum_i f^eq_i x_i^n, n = 2 .. 2K + 1, of a wavefront
+// whose sites all lie within the bound of a tier of K terms.  With b = 1 - a
+// they give
+//   S(a)  = sum_n (-1)^n b^n M_n / (n (n - 1)),
+//   S'(a) = -sum_n (-1)^n b^(n-1) M_n / (n - 1)
+// and D = S(0), all truncated where the tier truncates E and O, so that in
+// G(a) = S(a) - D the omitted terms cancel up to their factor b^(2K+2) - 1: a
+// solver's evaluation costs a short polynomial instead of a pass over the
+// directions.  Valid while |b| x stays about within the tier's bound `thr`
+// (fits()).
+template <class R, int K>
+struct PowerSums {
+  static constexpr int N = 2 * K + 2;
+  R M[N];
+  __device__ __forceinline__ static bool fits(R a, R xabs, R thr) {
+    return fabs(R(1) - a) * xabs <= R(1.15) * thr;
+  }
+  // with sA, also sum_i f^eq_i |x_i|
+  template <class V>
+  __device__ __forceinline__ void form(const V& v, R* sA = nullptr) {
+#pragma unroll
+    for (int n = 0; n < N; ++n) M[n] = R(0);
+    const auto P = v.pass_opaque();
+#pragma unroll
+    for (int i = 0; i < V::Q; ++i) {
+      const R xi = v.x(i, P), fi = v.fe(i, P);
+      if (sA) *sA = fma(fi, fabs(xi), *sA);
+      R w = fi * xi * xi;
+#pragma unroll
+      for (int n = 2; n < N; ++n) {
+        M[n] += w;
+        if (n + 1 < N) w *= xi;
+      }
+      // one direction's registers at a time
+      if constexpr (K > 4) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  __device__ __forceinline__ R S(R a) const {
+    const R b = R(1) - a;
+    R bn = b * b, Sv = R(0);
+#pragma unroll
+    for (int n = 2; n < N; ++n) {
+      Sv = fma(R((n % 2 ? -1.0 : 1.0) / (double(n) * (n - 1))) * bn, M[n], Sv);
+      bn *= b;
+    }
+    return Sv;
+  }
+  __device__ __forceinline__ R dS(R a) const {
+    const R b = R(1) - a;
+    R bn = b, v = R(0);
+#pragma unroll
+    for (int n = 2; n < N; ++n) {
+      v = fma(R((n % 2 ? 1.0 : -1.0) / (n - 1.0)) * bn, M[n], v);
+      bn *= b;
+    }
+    return v;
+  }
+};
+
 template <class R>
 struct AlphaOut {
   R alpha, D;
@@ -968,44 +1027,20 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
         // alpha^(0) = 1, so the first iterate is Eq. (9): G(1) = -D needs no
         // pass.  Later iterates take G from the populations held in
         // registers: where every active lane is on the common tier and two
-        // or more evaluations follow, from one pass forming the power sums
-        // M_n = sum_i f^eq_i x_i^n, n = 2 .. 2K + 1, which give
-        // S(a) = sum_n (-1)^n (1 - a)^n M_n / (n (n - 1)) truncated where
-        // the tier truncates E and O (the iterates lie in [1, 2], so
-        // |(1 - a) x_i| <= |x_i|); otherwise from Newton's passes (series
-        // where every lane's |(1 - a) x_i| allows it, else log1p).
-        constexpr int KS = Base<R>::K, NP = 2 * KS + 2;
+        // or more evaluations follow, from its power sums (the iterates lie
+        // in [1, 2], so |(1 - a) x_i| <= |x_i|); otherwise from Newton's
+        // passes (series where every lane's |(1 - a) x_i| allows it, else
+        // log1p).
         const bool poly = !is_rare_phase(PHASE) && d.secant_iters > 2 && __all(common);
-        R M[NP];
-#pragma unroll
-        for (int n = 0; n < NP; ++n) M[n] = R(0);
-        if (poly) {
-          const auto P = v.pass_opaque();
-#pragma unroll
-          for (int i = 0; i < Q; ++i) {
-            const R xi = v.x(i, P);
-            R w = v.fe(i, P) * xi * xi;
-#pragma unroll
-            for (int n = 2; n < NP; ++n) {
-              M[n] += w;
-              if (n + 1 < NP) w *= xi;
-            }
-            sched_group(i);
-          }
-        }
+        PowerSums<R, Base<R>::K> ps;
+        if (poly) ps.form(v);
         R a = R(1);
         for (int k = 0; k < d.secant_iters; ++k) {
           R Ga = -Dv;
           if (k > 0) {
             R Sv = R(0);
             if (poly) {
-              const R b = R(1) - a;
-              R bn = b * b;
-#pragma unroll
-              for (int n = 2; n < NP; ++n) {
-                Sv = fma(R((n % 2 ? -1.0 : 1.0) / (double(n) * (n - 1))) * bn, M[n], Sv);
-                bn *= b;
-              }
+              Sv = ps.S(a);
             } else {
               R dS, sA;
               S_dS_newton(v, a, xabs, Sv, dS, sA);
@@ -1021,17 +1056,22 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
       }
     } else if constexpr (MODE == kBisect) {
       // Eq. (4) on [1, alpha_max]; first midpoint with -tol <= G <= 0.  G is
-      // taken as in Newton's passes (series on the register-held
-      // populations where every lane allows it, else the log1p pass).  Pass
+      // taken from the power sums where they hold, else as in Newton's
+      // passes (series on the register-held populations where every lane
+      // allows it, else the log1p pass).  Pass
       // 0 asks whether G(alpha_max) <= 0 (then alpha = alpha_max); one call
       // site, so that the pass is inlined once.
+      const bool poly = __all(common);
+      PowerSums<R, Base<R>::K> ps;
+      if (poly) ps.form(v);
       R lo = R(1), hi = amax;
       const R tol = (R)d.root_tol;
       alpha = R(-1);
       for (int k = 0; k <= d.root_max_iter; ++k) {
         const R a = k == 0 ? amax : R(0.5) * (lo + hi);
         R Sv, dS, sA;
-        S_dS_newton(v, a, xabs, Sv, dS, sA);
+        if (poly && __all(ps.fits(a, xabs, Base<R>::thr))) Sv = ps.S(a);
+        else S_dS_newton(v, a, xabs, Sv, dS, sA);
         const R g = Sv - Dv;
         if (k == 0) {
           if (g <= R(0)) {
@@ -1062,47 +1102,75 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
       // below 1e-13 alpha (the rounding of G near the root moves alpha by
       // about that much); a converged Newton step that rounds onto the end
       // of the bracket stops there.
-      R lo = R(1), hi = amax;
-      bool hi_pos = false;  // G(hi) > 0 known
-      R a = (astar < amax) ? astar : R(0.5) * (lo + hi);
-      alpha = R(-1);
-      for (int k = 1; k <= d.root_max_iter; ++k) {
-        R Sv, dS, sA;
-        S_dS_newton(v, a, xabs, Sv, dS, sA);
-        const R gv = Sv - Dv;
-        iters = k;
-        if (fabs(gv) <= R(kEpsF64) * (R(1) + fabs(R(1) - a)) * sA) {
+      // eval(a, Sv, dS, sA) may decline a lane (false): solve() then leaves
+      // it unsolved, as does a bracket whose upper end has to be asked for
+      // while ask is false.
+      const auto solve = [&](R D, bool ask, const auto& eval) {
+        R lo = R(1), hi = amax;
+        bool hi_pos = false;  // G(hi) > 0 known
+        R a = (astar < amax) ? astar : R(0.5) * (lo + hi);
+        for (int k = 1; k <= d.root_max_iter; ++k) {
+          R Sv, dS, sA;
+          if (!eval(a, Sv, dS, sA)) return false;
+          const R gv = Sv - D;
+          iters = k;
           alpha = a;
-          break;
-        }
-        if (gv > R(0)) {
-          hi = a;
-          hi_pos = true;
-        } else {
-          lo = a;
-        }
-        R an = a - gv / dS;
-        if (!(an > lo && an < hi)) {
-          if (fabs(an - a) <= R(1e-13) * a) {
-            alpha = fmin(fmax(an, lo), hi);
-            break;
-          }
-          if (!hi_pos) {
-            if (S_log(v, hi) - Dv <= R(0)) {
-              alpha = hi;
-              break;
-            }
+          if (fabs(gv) <= R(kEpsF64) * (R(1) + fabs(R(1) - a)) * sA) return true;
+          if (gv > R(0)) {
+            hi = a;
             hi_pos = true;
+          } else {
+            lo = a;
           }
-          an = R(0.5) * (lo + hi);
-        }
-        if (fabs(an - a) <= R(1e-13) * a) {
+          R an = a - gv / dS;
+          if (!(an > lo && an < hi)) {
+            if (fabs(an - a) <= R(1e-13) * a) {
+              alpha = fmin(fmax(an, lo), hi);
+              return true;
+            }
+            if (!hi_pos) {
+              if (!ask) return false;
+              if (S_log(v, hi) - D <= R(0)) {
+                alpha = hi;
+                return true;
+              }
+              hi_pos = true;
+            }
+            an = R(0.5) * (lo + hi);
+          }
           alpha = an;
-          break;
+          if (fabs(an - a) <= R(1e-13) * a) return true;
+          a = an;
         }
-        a = an;
+        return true;  // the cap: the last iterate
+      };
+      // Where every lane lies within their bound, S and S' from the power
+      // sums of KP terms (truncation 2 x^(2KP+1) / ((2KP+3)(2KP+2)) below
+      // 2^-53): one pass instead of one per iteration.  In a loop of its own, so
+      // that the sums are not kept live through the passes of the other.  Five
+      // terms up to 0.05 with 19 and 27 directions (D3Q27 128^3 FP32, us per
+      // step: 211 -> 161, in turbulence with 6 % of the sites beyond 0.025 452
+      // -> 308; six terms up to 0.085 183 and 285, ten up to 0.2 spill: 674); the
+      // middle tier's four up to nine (D2Q9 2048^2 FP32 119 -> 101; five 107).
+      constexpr int KP = Q > 9 ? 5 : Base<R>::KM;
+      constexpr R thrP = Q > 9 ? R(0.05) : R(Base<R>::thrM);
+      bool solved = false;
+      if (__all(xabs <= thrP)) {
+        PowerSums<R, KP> ps;
+        R sA0 = R(0);
+        ps.form(v, &sA0);
+        solved = solve(ps.S(R(0)), false, [&](R a, R& Sv, R& dS, R& sA) {
+          Sv = ps.S(a);
+          dS = ps.dS(a);
+          sA = sA0;
+          return ps.fits(a, xabs, thrP);
+        });
       }
-      if (alpha < R(0)) alpha = a;
+      if (!solved)
+        solve(Dv, true, [&](R a, R& Sv, R& dS, R& sA) {
+          S_dS_newton(v, a, xabs, Sv, dS, sA);
+          return true;
+        });
     }
   }
   o.alpha = alpha;
