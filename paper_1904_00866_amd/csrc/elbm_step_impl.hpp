@@ -729,24 +729,28 @@ __device__ __forceinline__ void S_dS_newton(const V& v, R a, R xabs, R& Sv, R& d
   S_dS_log(v, a, Sv, dS, &sA);
 }
 
-// The rare path of one lane: the long series when alpha_* = 2 and
-// max|x| <= thrL, else the log1p forms.
+// The rare tier of one lane.  far_sums: max|x_i|, max x_i and the long
+// series' E and O in one sweep (the sums hold up to max|x_i| <= thrL, where
+// alpha_* = 2; in two sweeps four restart steps of D3Q27 100 x 90 x 70 FP64 with
+// their readings took 472 us, now 439); log_sums: the log1p forms beyond.
 template <bool REREAD, class V, class R>
-__device__ __forceinline__ void rare_sums(const V& v, R astar, bool star2, R xabs, R& Dv, R& Ds,
-                          R& Gs) {
-  if (star2 && xabs <= Base<R>::thrL) {
-    R sE = R(0), sO = R(0);
-    const SeriesK<R, Base<R>::KL> ser;
-    v.template sweep<REREAD>([&](int, R, R xi, R fi, R) { ser.accum(xi, fi, sE, sO); });
-    R cE, cO;
-    series_scale<R, Base<R>::KL>(cE, cO);
-    sE *= cE;
-    sO *= cO;
-    Dv = sE - sO;
-    Ds = sE + sO;
-    Gs = R(2) * sO;
-    return;
-  }
+__device__ __forceinline__ void far_sums(const V& v, R& xabs, R& xmax, R& E, R& O) {
+  R sE = R(0), sO = R(0), xa = R(0), xm = R(-1);
+  const SeriesK<R, Base<R>::KL> ser;
+  v.template sweep<REREAD>([&](int, R, R xi, R fi, R) {
+    xa = fmax(xa, fabs(xi));
+    xm = fmax(xm, xi);
+    ser.accum(xi, fi, sE, sO);
+  });
+  R cE, cO;
+  series_scale<R, Base<R>::KL>(cE, cO);
+  xabs = xa;
+  xmax = xm;
+  E = sE * cE;
+  O = sO * cO;
+}
+template <bool REREAD, class V, class R>
+__device__ __forceinline__ void log_sums(const V& v, R astar, R& Dv, R& Ds, R& Gs) {
   R sD = R(0), sS = R(0), sG = R(0);
   v.template sweep<REREAD>([&](int, R, R xi, R fi, R) {
     const R px = phi_log<R>(xi);
@@ -945,11 +949,8 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
       sO *= cO;
     }
   } else {
-    // only deferred lanes are active: max|x_i| again, and max x_i
-    v.template sweep<kReread>([&](int, R, R xi, R, R) {
-      xabs = fmax(xabs, fabs(xi));
-      xmax = fmax(xmax, xi);
-    });
+    // only deferred lanes are active
+    far_sums<kReread>(v, xabs, xmax, sE, sO);
   }
   // D = H(f) - H(f^eq), Gs = H(f*(a_*)) - H(f), Ds = H(f*(a_*)) - H(f^eq); at
   // alpha_* = 2: D = E - O, Ds = E + O, Gs = 2 O.
@@ -989,8 +990,14 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
   if constexpr (PHASE == kPhaseCommon) {
     if (rare) return o;
   }
-  if constexpr (PHASE == kPhaseAll && !kXmax) {
-    if (rare) v.template sweep<kReread>([&](int, R, R xi, R, R) { xmax = fmax(xmax, xi); });
+  if constexpr (PHASE == kPhaseAll) {
+    if (rare) {
+      R E, O;
+      far_sums<kReread>(v, xabs, xmax, E, O);
+      Dv = E - O;
+      Ds = E + O;
+      Gs = R(2) * O;
+    }
   }
   // alpha_max = min over {f^eq_i < f_i} of f_i/(f_i - f^eq_i) = 1 + 1/max_i x_i
   // (definition after Eq. (7)); alpha_* = min(2, alpha_max) (Eq. (8)), and
@@ -1001,9 +1008,7 @@ __device__ __forceinline__ AlphaOut<typename V::Real> choose_alpha(V& v, const S
   const bool star2 = (rare || kXmax) ? !(xmax > R(1)) : true;
   const R astar = star2 ? R(2) : amax;
   o.fallback = rare;
-  if (__any(rare)) {
-    if (rare) rare_sums<kReread>(v, astar, star2, xabs, Dv, Ds, Gs);
-  }
+  if (rare && !(star2 && xabs <= Base<R>::thrL)) log_sums<kReread>(v, astar, Dv, Ds, Gs);
   // f = f^eq to rounding: the paper leaves alpha free there; take alpha_*.
   const bool guard = !has_pos || !(Dv > Prec<R>::guard * v.rho);
   o.D = Dv;
@@ -2009,8 +2014,11 @@ __device__ __forceinline__ uint32_t site_update_rare(const SimDesc& d,
 // VGPRs: the decoded deviations and the per-axis factors of both the
 // equilibrium and its reciprocal; four waves spill in the common path and
 // run 5.02 ms against 3.86 ms at 512^3 with mixed arithmetic).
-template <class S, int MODE>
+// Mixed arithmetic on 2-byte storage, up to nine directions: six, which its
+// common path fits (78 VGPRs); five cost 2.5 % at 4096^2.
+template <class S, int MODE, class AP = double, int Q = 27, bool SUMS = true>
 constexpr int step_waves() {
+  if (sizeof(typename S::T) == 2 && MODE == kClosed && kIsMixed<AP> && Q <= 9 && !SUMS) return 6;
   if (sizeof(typename S::T) == 2 && MODE == kClosed) return 3;
   if (sizeof(typename S::T) <= 4 && (MODE == kClosed || MODE == kBGK)) return ELBM_CLOSED_WAVES;
   if (sizeof(typename S::T) <= 4 && (MODE == kNewton || MODE == kSecant || MODE == kBisect))
@@ -2019,7 +2027,7 @@ constexpr int step_waves() {
 }
 
 template <int D, class S, int MODE, class R, bool SUMS, int ELBM_TILES>
-__global__ void __launch_bounds__(kBlock, (step_waves<S, MODE>())) k_step(const BatchArgs args) {
+__global__ void __launch_bounds__(kBlock, (step_waves<S, MODE, R, Lattice<D>::Q, SUMS>())) k_step(const BatchArgs args) {
   using T = typename S::T;
   constexpr int Q = Lattice<D>::Q;
   constexpr int kSplit = tiles_per_block(sizeof(T), Q) / ELBM_TILES;  // workgroups per described one
