@@ -43,7 +43,8 @@ def log(msg: str) -> None:
 
 
 # Sources that make up the step kernels (host runtime and server excluded).
-STEP_KERNEL_SOURCES = ("elbm_internal.hpp", "elbm_site.hpp", "elbm_step_impl.hpp",
+STEP_KERNEL_SOURCES = ("elbm_internal.hpp", "elbm_site.hpp", "elbm_pull.hpp",
+                       "elbm_step_impl.hpp",
                        "elbm_step_d1.hip", "elbm_step_d2.hip", "elbm_step_d3.hip")
 
 

@@ -206,7 +206,10 @@ elbm_status elbm_init(const elbm_config *cfg, const double *rho0,
  * f[Q*N] float64 (non-negative for the entropic modes).  t is unchanged. */
 elbm_status elbm_set_populations(elbm_sim *sim, const double *f);
 
-/* Advance nsteps >= 0 time steps (Eq. (1) then Eq. (5b) per step). */
+/* Advance nsteps >= 0 time steps (Eq. (1) then Eq. (5b) per step).  Steps
+ * that record nothing may share a kernel launch; the results are those of
+ * single steps, bit for bit, and the state ends in the same part of the state
+ * buffer (a captured call of an even number of steps can be replayed). */
 elbm_status elbm_step(elbm_sim *sim, int64_t nsteps);
 
 /* The moments of the current f(x,t) that the equilibrium is constrained to
@@ -274,10 +277,10 @@ elbm_status elbm_import(elbm_sim *sim, const void *src, size_t bytes, int64_t t)
 /* Message of the calling thread's last error ("" if none). */
 const char *elbm_last_error(void);
 
-/* Advance several independent simulations that share one stream with ONE
- * kernel launch per step: sims[n] all created on the same stream with the
- * same lattice, storage, alpha mode and arithmetic; nsteps[n] (host) steps
- * each, sims with fewer steps drop out as they finish.  Results are
+/* Advance several independent simulations that share one stream with at most
+ * ONE kernel launch per step (and per 16 simulations): sims[n] all created on
+ * the same stream with the same lattice, storage, alpha mode and arithmetic;
+ * nsteps[n] (host) steps each, sims with fewer steps drop out as they finish.  Results are
  * identical to stepping each simulation alone. */
 elbm_status elbm_step_batch(elbm_sim *const *sims, const int64_t *nsteps,
                             int32_t n);
@@ -318,7 +321,7 @@ elbm_status elbm_step_noalloc(elbm_sim *sim, int64_t nsteps, uint32_t diag,
  * and the pool has room for the request's state (elbm_state_bytes) plus a
  * staging copy of its initial fields.  Each scheduling round advances every
  * resident simulation by up to round_steps steps with batched launches
- * (elbm_step_batch: one launch per step for all residents of the same
+ * (elbm_step_batch: at most one launch per step for all residents of the same
  * lattice, storage, alpha mode and arithmetic); a request arriving while a
  * round runs joins at the next round.  Two rounds are kept in flight on the
  * stream, so admission and completion work on the host overlaps the GPU.
@@ -377,7 +380,8 @@ typedef struct {
 
 typedef struct {
   int64_t submitted, completed, failed;
-  int64_t rounds, launches;
+  int64_t rounds, launches; /* launches: batched steps, an upper bound of
+                           the kernel launches (steps may share one)         */
   int64_t site_updates; /* sum over completed steps of the box sizes         */
   int64_t max_resident; /* most simulations resident at once                 */
   double t_first_submit, t_last_done;

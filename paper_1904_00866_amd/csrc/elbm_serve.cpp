@@ -15,7 +15,7 @@
 //      preempted request needs only its state block and continues from its
 //      checkpoint;
 //   4. launches one round: up to round_steps steps of every resident
-//      simulation, one batched launch per step for each group of residents
+//      simulation, at most one batched launch per step for each group of residents
 //      that share a kernel (lattice, storage, alpha mode, arithmetic), then
 //      the final moments of the requests that finish, then an event.
 // With two rounds in flight the host work of 1-3 overlaps the GPU.  All
@@ -344,7 +344,7 @@ void launch_round(elbm_server* s, std::unique_lock<std::mutex>& lk) {
       err = std::string("step launch: ") + elbm_last_error();
       break;
     }
-    // one launch per step and per kMaxBatch simulations still stepping
+    // counted as one launch per step and per kMaxBatch simulations still stepping
     std::sort(steps.begin(), steps.end());
     int64_t prev = 0;
     for (size_t k = 0; k < steps.size(); ++k) {

@@ -311,7 +311,7 @@ def stats_from_bytes(raw) -> dict:
 
 def step_batch(sims, nsteps):
     """Advance several simulations (same stream, lattice, storage, mode) with
-    one kernel launch per step."""
+    one kernel launch per step at most."""
     n = len(sims)
     hs = (C.c_void_p * n)(*[s.handle for s in sims])
     ns = (C.c_int64 * n)(*[int(k) for k in nsteps])
