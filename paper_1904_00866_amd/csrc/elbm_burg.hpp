@@ -13,7 +13,7 @@ namespace elbm {
 
 // Index of the direction -c_i (digits 1 and 2 swapped).
 template <class L>
-constexpr int opposite(int i) {
+__host__ __device__ constexpr int opposite(int i) {
   return Dirs<L>::index((3 - L::dg(i, 0)) % 3, (3 - L::dg(i, 1)) % 3, (3 - L::dg(i, 2)) % 3);
 }
 

@@ -116,6 +116,19 @@ __device__ __forceinline__ double S_chi(const SiteBurg<L, S>& v, double a, doubl
   return s;
 }
 
+// Nonzero components of c_i, which give the weight, and the first direction
+// with n of them (-1: none).
+template <class L>
+__host__ __device__ constexpr int nonzeros(int i) {
+  return (L::c(i, 0) != 0) + (L::c(i, 1) != 0) + (L::c(i, 2) != 0);
+}
+template <class L>
+__host__ __device__ constexpr int first_of_class(int n) {
+  for (int i = 0; i < L::Q; ++i)
+    if (nonzeros<L>(i) == n) return i;
+  return -1;
+}
+
 // Series tier: max|x_i| <= kThrB keeps the alpha error of the K-term sums
 // below 2^-53 (truncation moves alpha by about 4 x^(2K+1) / (2K+3)).
 constexpr int kKB = 4;
@@ -126,7 +139,8 @@ __device__ __forceinline__ AlphaOut<double> choose_alpha_burg(SiteBurg<L, S>& v,
   constexpr int Q = L::Q;
   AlphaOut<double> o;
   o.deferred = false;
-  double xmax = -1.0, xabs = 0.0, sE = 0.0, sO = 0.0;
+  // sums per weight class (n nonzero components of c_i), weighted at the end
+  double xmax = -1.0, xabs = 0.0, eS[4] = {0.0, 0.0, 0.0, 0.0}, oS[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     const double xi = v.x[i], t = xi * xi;
@@ -139,8 +153,17 @@ __device__ __forceinline__ AlphaOut<double> choose_alpha_burg(SiteBurg<L, S>& v,
       pe = fma(pe, t, 1.0 / (2.0 * k));
       po = fma(po, t, 1.0 / (2.0 * k + 1.0));
     }
-    sE = fma(L::W(i) * t, pe, sE);
-    sO = fma(L::W(i) * t * xi, po, sO);
+    const int n = nonzeros<L>(i);
+    eS[n] = fma(t, pe, eS[n]);
+    oS[n] = fma(t * xi, po, oS[n]);
+  }
+  double sE = 0.0, sO = 0.0;
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    const int n = nonzeros<L>(i);
+    if (first_of_class<L>(n) != i) continue;
+    sE = fma(L::W(i), eS[n], sE);
+    sO = fma(L::W(i), oS[n], sO);
   }
   const bool rare = !(xabs <= kThrB);
   const bool has_pos = xmax > 0.0;
@@ -286,13 +309,30 @@ __device__ __forceinline__ uint32_t update_burg(const SimDesc& d, typename S::T*
   double ftmin = INFINITY;
   const uint32_t lo = (s & 63u) * es;
   const gaddr blk = block_base<Q>(dst, s);
-#pragma unroll
-  for (int i = 0; i < Q; ++i) {
+  // f^eq_i = W_i / d_i by pairs (c, -c): one reciprocal of d_+ d_- for both
+  // (a reciprocal issues at a quarter of the rate and takes four refinement
+  // steps; what bounds this kernel is the issue of its FP64 instructions: with
+  // one per direction and the weights applied in every term of the series sums
+  // 344 us a step at 160^3 FP32, now 334).  The root solvers, which are short
+  // of registers, keep one per direction (D3Q19 Newton 1.3 % slower in pairs).
+  constexpr bool kPairs = MODE == kClosed;
+  const auto put = [&](int i, double r) {
     const double gi = v.g(i);
-    const double fe = L::W(i) * rcp_n<double>(v.den(i));
-    const double ft = fma(ab, fe - gi, gi);
+    const double ft = fma(ab, fma(L::W(i), r, -gi), gi);
     ftmin = fmin(ftmin, ft);
     st_nt<T>(blk + i * kLane * es, kLane * es, lo, Codec<S, double>::enc(ft, L::invW(i), v.rho_ref));
+  };
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    const int io = opposite<L>(i);
+    if (kPairs && io < i) continue;  // the pair was taken at io
+    if (!kPairs || io == i) {
+      put(i, rcp_n<double>(v.den(i)));
+      continue;
+    }
+    const double dp = v.den(i), dm = v.den(io), r = rcp_n<double>(dp * dm);
+    put(i, dm * r);
+    put(io, dp * r);
   }
   return record_site<SUMS>(d, s, live, v, ao, ftmin, j, acc, diag);
 }
