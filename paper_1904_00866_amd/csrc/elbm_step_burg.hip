@@ -309,13 +309,17 @@ __device__ __forceinline__ uint32_t update_burg(const SimDesc& d, typename S::T*
   double ftmin = INFINITY;
   const uint32_t lo = (s & 63u) * es;
   const gaddr blk = block_base<Q>(dst, s);
-  // f^eq_i = W_i / d_i by pairs (c, -c): one reciprocal of d_+ d_- for both
-  // (a reciprocal issues at a quarter of the rate and takes four refinement
-  // steps; what bounds this kernel is the issue of its FP64 instructions: with
-  // one per direction and the weights applied in every term of the series sums
-  // 344 us a step at 160^3 FP32, now 334).  The root solvers, which are short
-  // of registers, keep one per direction (D3Q19 Newton 1.3 % slower in pairs).
-  constexpr bool kPairs = MODE == kClosed;
+  // f^eq_i = W_i / d_i.  With 4-byte storage, where the result is rounded to 24
+  // bits, by pairs (c, -c): one reciprocal of d_+ d_- for both (a reciprocal
+  // issues at a quarter of the rate and takes four refinement steps; what
+  // bounds this kernel is the issue of its FP64 instructions: 160^3 FP32 343 us
+  // a step with one per direction, 330 with pairs; errors against 80-bit
+  // arithmetic the same to four digits).  With FP64 storage the two further
+  // roundings of a pair show: 4 to 8 % more rms error in the new populations
+  // on every lattice, near and far from equilibrium, for 2 % of the time, so
+  // it keeps one reciprocal per direction.  So do the root solvers, which are
+  // short of registers (D3Q19 Newton 1.3 % slower in pairs).
+  constexpr bool kPairs = MODE == kClosed && sizeof(T) < 8;
   const auto put = [&](int i, double r) {
     const double gi = v.g(i);
     const double ft = fma(ab, fma(L::W(i), r, -gi), gi);
