@@ -285,6 +285,12 @@ const char *elbm_last_error(void);
 elbm_status elbm_step_batch(elbm_sim *const *sims, const int64_t *nsteps,
                             int32_t n);
 
+/* Kernel launches that elbm_step_batch makes on n simulations of these
+ * configurations (n = 1: those of elbm_step), nsteps[k] steps each.  Host
+ * only; -1 where a configuration or the batch is invalid. */
+int64_t elbm_batch_launches(const elbm_config *cfgs, const int64_t *nsteps,
+                            int32_t n);
+
 /* ---- a step with diagnostics that allocates nothing ---------------------
  *
  * For callers that cannot allocate device memory or hand the library a
@@ -380,8 +386,7 @@ typedef struct {
 
 typedef struct {
   int64_t submitted, completed, failed;
-  int64_t rounds, launches; /* launches: batched steps, an upper bound of
-                           the kernel launches (steps may share one)         */
+  int64_t rounds, launches; /* launches: kernel launches of the batched steps */
   int64_t site_updates; /* sum over completed steps of the box sizes         */
   int64_t max_resident; /* most simulations resident at once                 */
   double t_first_submit, t_last_done;

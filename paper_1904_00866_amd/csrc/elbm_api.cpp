@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstddef>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -403,6 +404,57 @@ elbm_status check_sim(const elbm_sim* s) {
   return ELBM_OK;
 }
 
+elbm_status check_batch(elbm_sim* const* sims, const int64_t* nsteps, int32_t n) {
+  for (int32_t k = 0; k < n; ++k) {
+    const elbm_sim *s0 = sims[0], *s = sims[k];
+    if (!s) return fail(ELBM_EINVAL, "batch entry %d is NULL", k);
+    if (nsteps[k] < 0) return fail(ELBM_EINVAL, "batch entry %d: nsteps < 0", k);
+    if (s->L.lattice != s0->L.lattice || s->cfg.storage != s0->cfg.storage ||
+        s->cfg.alpha_mode != s0->cfg.alpha_mode || s->cfg.alpha_fp64 != s0->cfg.alpha_fp64 ||
+        s->cfg.entropy != s0->cfg.entropy)
+      return fail(ELBM_EINVAL, "batch entry %d: lattice/storage/mode/precision/entropy differ", k);
+    if (s->stream != s0->stream || s->device != s0->device)
+      return fail(ELBM_EINVAL, "batch entry %d: different stream or device", k);
+    for (int32_t m = 0; m < k; ++m)
+      if (sims[m] == s) return fail(ELBM_EINVAL, "batch entry %d repeats entry %d", k, m);
+  }
+  return ELBM_OK;
+}
+
+// The launches that advance simulation k of a batch by nsteps[k] steps, in
+// order: launch(sims, last, n, f) advances n <= kMaxBatch of them by f.steps()
+// (as launch_steps does).
+template <class Launch>
+hipError_t for_each_launch(elbm_sim* const* sims, const int64_t* nsteps, int32_t n,
+                           const Launch& launch) {
+  int64_t kmax = 0;
+  for (int32_t k = 0; k < n; ++k) kmax = std::max(kmax, nsteps[k]);
+  std::vector<elbm_sim*> active;
+  std::vector<char> last;  // this step is the simulation's last of the call
+  active.reserve(size_t(n));
+  last.reserve(size_t(n));
+  for (int64_t step = 0; step < kmax;) {
+    active.clear();
+    int64_t free = kmax;
+    for (int32_t k = 0; k < n; ++k)
+      if (nsteps[k] > step) {
+        active.push_back(sims[k]);
+        free = std::min(free, free_steps(sims[k], nsteps[k] - step));
+      }
+    const Fusion f = fusion_of(active.data(), active.size(), free);
+    last.clear();
+    for (int32_t k = 0; k < n; ++k)
+      if (nsteps[k] > step) last.push_back(nsteps[k] == step + f.steps());
+    for (size_t c0 = 0; c0 < active.size(); c0 += kMaxBatch) {
+      const size_t c = std::min(active.size() - c0, size_t(kMaxBatch));
+      const hipError_t e = launch(active.data() + c0, last.data() + c0, c, f);
+      if (e != hipSuccess) return e;
+    }
+    step += f.steps();
+  }
+  return hipSuccess;
+}
+
 }  // namespace
 
 extern "C" {
@@ -459,6 +511,26 @@ void release_sim(elbm_sim* sim) { delete sim; }
 
 // Set the calling thread's error message.
 elbm_status set_error(elbm_status st, const char* msg) { return fail(st, "%s", msg); }
+
+// elbm_step_batch; *launches receives the kernel launches it has made.
+elbm_status step_batch(elbm_sim* const* sims, const int64_t* nsteps, int32_t n,
+                       int64_t* launches) try {
+  *launches = 0;
+  if (n < 0 || (n > 0 && (!sims || !nsteps))) return fail(ELBM_EINVAL, "bad batch arguments");
+  if (n == 0) return ELBM_OK;
+  const elbm_status st = check_batch(sims, nsteps, n);
+  if (st != ELBM_OK) return st;
+  DeviceGuard g(sims[0]->device);
+  if (!g.ok) return fail(ELBM_EDEVICE, "cannot select the simulations' device");
+  const hipError_t e = for_each_launch(
+      sims, nsteps, n, [&](elbm_sim* const* s, const char* last, size_t c, const Fusion& f) {
+        *launches += f.launches();
+        return launch_steps(s, last, c, f);
+      });
+  return e == hipSuccess ? ELBM_OK : hip_fail(e, "batched step kernel launch");
+} catch (const std::bad_alloc&) {
+  return fail(ELBM_ENOMEM, "out of host memory");
+}
 
 }  // namespace elbm
 
@@ -635,50 +707,35 @@ elbm_status elbm_step(elbm_sim* s, int64_t nsteps) {
 }
 
 elbm_status elbm_step_batch(elbm_sim* const* sims, const int64_t* nsteps, int32_t n) {
-  if (n < 0 || (n > 0 && (!sims || !nsteps))) return fail(ELBM_EINVAL, "bad batch arguments");
-  if (n == 0) return ELBM_OK;
-  const elbm_sim* s0 = sims[0];
-  int64_t kmax = 0;
+  int64_t launches;
+  return elbm::step_batch(sims, nsteps, n, &launches);
+}
+
+int64_t elbm_batch_launches(const elbm_config* cfgs, const int64_t* nsteps, int32_t n) try {
+  if (n < 0 || (n > 0 && (!cfgs || !nsteps))) {
+    fail(ELBM_EINVAL, "bad batch arguments");
+    return -1;
+  }
+  std::vector<std::unique_ptr<elbm_sim>> own;  // handles that no device work uses
+  std::vector<elbm_sim*> sims;
   for (int32_t k = 0; k < n; ++k) {
-    const elbm_sim* s = sims[k];
-    if (!s) return fail(ELBM_EINVAL, "batch entry %d is NULL", k);
-    if (nsteps[k] < 0) return fail(ELBM_EINVAL, "batch entry %d: nsteps < 0", k);
-    if (s->L.lattice != s0->L.lattice || s->cfg.storage != s0->cfg.storage ||
-        s->cfg.alpha_mode != s0->cfg.alpha_mode || s->cfg.alpha_fp64 != s0->cfg.alpha_fp64 ||
-        s->cfg.entropy != s0->cfg.entropy)
-      return fail(ELBM_EINVAL, "batch entry %d: lattice/storage/mode/precision/entropy differ", k);
-    if (s->stream != s0->stream || s->device != s0->device)
-      return fail(ELBM_EINVAL, "batch entry %d: different stream or device", k);
-    for (int32_t m = 0; m < k; ++m)
-      if (sims[m] == s) return fail(ELBM_EINVAL, "batch entry %d repeats entry %d", k, m);
-    if (nsteps[k] > kmax) kmax = nsteps[k];
+    Layout L;
+    if (check_config(&cfgs[k], &L) != ELBM_OK) return -1;
+    own.emplace_back(new_handle(&cfgs[k], L, nullptr, nullptr, 0));
+    if (!own.back()) throw std::bad_alloc();
+    sims.push_back(own.back().get());
   }
-  DeviceGuard g(s0->device);
-  if (!g.ok) return fail(ELBM_EDEVICE, "cannot select the simulations' device");
-  std::vector<elbm_sim*> active;
-  std::vector<char> last;  // this step is the simulation's last of the call
-  active.reserve(size_t(n));
-  last.reserve(size_t(n));
-  for (int64_t step = 0; step < kmax;) {
-    active.clear();
-    int64_t free = kmax;
-    for (int32_t k = 0; k < n; ++k)
-      if (nsteps[k] > step) {
-        active.push_back(sims[k]);
-        free = std::min(free, free_steps(sims[k], nsteps[k] - step));
-      }
-    const Fusion f = fusion_of(active.data(), active.size(), free);
-    last.clear();
-    for (int32_t k = 0; k < n; ++k)
-      if (nsteps[k] > step) last.push_back(nsteps[k] == step + f.steps());
-    for (size_t c0 = 0; c0 < active.size(); c0 += kMaxBatch) {
-      const size_t c = std::min(active.size() - c0, size_t(kMaxBatch));
-      const hipError_t e = launch_steps(active.data() + c0, last.data() + c0, c, f);
-      if (e != hipSuccess) return hip_fail(e, "batched step kernel launch");
-    }
-    step += f.steps();
-  }
-  return ELBM_OK;
+  if (check_batch(sims.data(), nsteps, n) != ELBM_OK) return -1;
+  int64_t launches = 0;
+  (void)for_each_launch(sims.data(), nsteps, n,
+                        [&](elbm_sim* const*, const char*, size_t, const Fusion& f) {
+                          launches += f.launches();
+                          return hipSuccess;
+                        });
+  return launches;
+} catch (const std::bad_alloc&) {
+  fail(ELBM_ENOMEM, "out of host memory");
+  return -1;
 }
 
 elbm_status elbm_step_noalloc(elbm_sim* s, int64_t nsteps, uint32_t diag,

@@ -50,6 +50,7 @@ elbm_status set_error(elbm_status st, const char* msg);
 elbm_status resume_sim(const elbm_config* cfg, void* dev_state, size_t bytes, void* hip_stream,
                        const void* host_ckpt, size_t ckpt_bytes, int64_t t, elbm_sim** out);
 elbm_status checkpoint_to_host(elbm_sim* sim, void* host_dst, size_t bytes, int64_t* t);
+elbm_status step_batch(elbm_sim* const* sims, const int64_t* nsteps, int32_t n, int64_t* launches);
 }  // namespace elbm
 
 using elbm::set_error;
@@ -340,17 +341,13 @@ void launch_round(elbm_server* s, std::unique_lock<std::mutex>& lk) {
       steps.push_back(todo[order[k]]);
       rd.updates += todo[order[k]] * act[order[k]]->N;
     }
-    if (elbm_step_batch(sims.data(), steps.data(), (int32_t)sims.size()) != ELBM_OK) {
+    int64_t made = 0;
+    const elbm_status st =
+        elbm::step_batch(sims.data(), steps.data(), (int32_t)sims.size(), &made);
+    launches += made;
+    if (st != ELBM_OK) {
       err = std::string("step launch: ") + elbm_last_error();
       break;
-    }
-    // counted as one launch per step and per kMaxBatch simulations still stepping
-    std::sort(steps.begin(), steps.end());
-    int64_t prev = 0;
-    for (size_t k = 0; k < steps.size(); ++k) {
-      const int64_t left = int64_t(steps.size() - k);
-      launches += (steps[k] - prev) * ((left + elbm::kMaxBatch - 1) / elbm::kMaxBatch);
-      prev = steps[k];
     }
   }
   std::vector<char> fin(act.size(), 0);

@@ -34,7 +34,8 @@ STATUS = {0: "ELBM_OK", -1: "ELBM_EINVAL", -2: "ELBM_EDEVICE", -3: "ELBM_ENOMEM"
 EXPORTS = ["elbm_config_default", "elbm_state_bytes", "elbm_init", "elbm_set_populations",
            "elbm_step", "elbm_moments", "elbm_populations", "elbm_gather",
            "elbm_alpha_field", "elbm_stats", "elbm_time", "elbm_destroy",
-           "elbm_last_error", "elbm_step_batch", "elbm_server_create", "elbm_server_submit",
+           "elbm_last_error", "elbm_step_batch", "elbm_batch_launches", "elbm_server_create",
+           "elbm_server_submit",
            "elbm_server_poll", "elbm_server_wait", "elbm_server_sim", "elbm_server_release",
            "elbm_server_cancel",
            "elbm_server_get_stats", "elbm_server_destroy", "elbm_checkpoint_bytes",
@@ -122,6 +123,8 @@ def lib():
         L.elbm_last_error.argtypes = []
         L.elbm_last_error.restype = C.c_char_p
         L.elbm_step_batch.argtypes = [C.POINTER(vp), C.POINTER(C.c_int64), C.c_int32]
+        L.elbm_batch_launches.argtypes = [cfgp, C.POINTER(C.c_int64), C.c_int32]
+        L.elbm_batch_launches.restype = C.c_int64
         L.elbm_server_create.argtypes = [C.POINTER(ServerConfig), C.POINTER(vp)]
         L.elbm_server_submit.argtypes = [vp, C.POINTER(Request), C.POINTER(C.c_int64)]
         L.elbm_server_poll.argtypes = [vp, C.c_int64, C.POINTER(RequestInfo)]
@@ -140,6 +143,7 @@ def lib():
             getattr(L, name).restype = getattr(L, name).restype or C.c_int
         L.elbm_state_bytes.restype = C.c_size_t
         L.elbm_time.restype = C.c_int64
+        L.elbm_batch_launches.restype = C.c_int64
         L.elbm_last_error.restype = C.c_char_p
         _lib = L
     return _lib
@@ -316,6 +320,17 @@ def step_batch(sims, nsteps):
     hs = (C.c_void_p * n)(*[s.handle for s in sims])
     ns = (C.c_int64 * n)(*[int(k) for k in nsteps])
     _check(lib().elbm_step_batch(hs, ns, n))
+
+
+def batch_launches(cfgs, nsteps) -> int:
+    """Kernel launches of step_batch on simulations of these configurations
+    (one configuration: of Simulation.step).  No device is used."""
+    n = len(cfgs)
+    launches = lib().elbm_batch_launches((Config * n)(*cfgs),
+                                         (C.c_int64 * n)(*[int(k) for k in nsteps]), n)
+    if launches < 0:
+        _check(-1)
+    return launches
 
 
 class KeptSimulation(Simulation):

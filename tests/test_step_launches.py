@@ -1,0 +1,47 @@
+"""How many kernel launches steps take (host only: no device work)."""
+import pytest
+
+from paper_1904_00866_amd import elbm
+
+
+def launches(boxes, steps, lattice="d2q9", **kw):
+    cfgs = [elbm.make_config(lattice, *b, **kw) for b in boxes]
+    return elbm.batch_launches(cfgs, steps)
+
+
+def test_one_launch_per_step_where_nothing_is_fused():
+    """Lattices, modes and entropies without a fused kernel; a step that records."""
+    for lattice, box in (("d1q3", (640,)), ("d3q27", (8, 8, 8)), ("d3q19", (8, 8, 8))):
+        assert launches([box], [7], lattice) == 7
+    for kw in (dict(mode="newton"), dict(mode="secant"), dict(entropy="burg")):
+        assert launches([(64, 64)], [7], **kw) == 7
+    assert launches([(64, 64)], [1], diag=elbm.DIAG_COUNTS) == 1
+    assert launches([(64, 64)], [0]) == 0 and launches([], []) == 0
+
+
+def test_fused_steps_share_launches():
+    """64^2: five steps a launch (six would have to come in pairs); the recording
+    last step is a launch of its own."""
+    assert launches([(64, 64)], [10], storage="f64") == 2
+    assert launches([(64, 64)], [11], storage="f64", diag=elbm.DIAG_COUNTS) == 3
+    assert launches([(64, 64)], [12], storage="f64") == 2  # six and six
+
+
+def test_batch_of_different_lengths():
+    """Simulations that record and end at different steps; more than sixteen
+    share no launch."""
+    d = elbm.DIAG_COUNTS
+    assert launches([(8, 8, 8)] * 3, [2, 5, 0], "d3q27", diag=d) == 5
+    assert launches([(8, 8, 8)] * 17, [4] * 17, "d3q27") == 8
+
+
+def test_invalid_batches():
+    cfg = elbm.make_config("d2q9", 64, 64)
+    with pytest.raises(elbm.ElbmError, match="nsteps < 0"):
+        elbm.batch_launches([cfg], [-1])
+    with pytest.raises(elbm.ElbmError, match="differ"):
+        elbm.batch_launches([cfg, elbm.make_config("d2q9", 64, 64, storage="f64")], [1, 1])
+    bad = elbm.make_config("d2q9", 64, 64)
+    bad.reserved = 1
+    with pytest.raises(elbm.ElbmError, match="reserved"):
+        elbm.batch_launches([bad], [1])
