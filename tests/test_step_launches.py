@@ -35,6 +35,18 @@ def test_batch_of_different_lengths():
     assert launches([(8, 8, 8)] * 17, [4] * 17, "d3q27") == 8
 
 
+@pytest.mark.parametrize("n,kw", [(64, dict(storage="f32")),
+                                  (128, dict(storage="f16dev", fp64="mixed")),
+                                  (128, dict(storage="f32", fp64="mixed")),
+                                  (128, dict(storage="f64"))])
+def test_groups_of_sixteen_choose_for_themselves(n, kw):
+    """Sixteen simulations share a launch: more of them change no group's choice."""
+    one = launches([(n, n)] * 16, [60] * 16, **kw)
+    assert launches([(n, n)] * 64, [60] * 64, **kw) == 4 * one
+    rest = launches([(n, n)] * 8, [60] * 8, **kw)
+    assert launches([(n, n)] * 40, [60] * 40, **kw) == 2 * one + rest
+
+
 def test_invalid_batches():
     cfg = elbm.make_config("d2q9", 64, 64)
     with pytest.raises(elbm.ElbmError, match="nsteps < 0"):
