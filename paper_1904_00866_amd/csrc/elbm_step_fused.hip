@@ -154,30 +154,29 @@ __global__ void __launch_bounds__(64 * WAVES) k_fused(const BatchArgs args, int 
     __syncthreads();
   }
   const gaddr base = buffer_base(dst);
-  // The places that pad the last tile of kBlock sites hold site 0's new
-  // populations after a single step (its lanes past the box repeat that site).
-  // A checkpoint copies them too, so they are written here as well, by the
-  // workgroup of site 0: every wavefront the same values (the lane number
-  // comes from the hardware; keeping the thread's through the steps costs the
-  // register that takes the FP32 32 x 32 kernel from four waves per SIMD to
-  // three.  Beside the stores, not after them: at the kernel's end its check
-  // alone took 0.08 us of a launch, the fetch of one more line of code).
-  if (__builtin_expect(x0 == -frame && y0 == -frame && nx * ny % kBlock != 0, 0)) {
-    __syncthreads();
-    const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-    const uint32_t N = nx * ny, end = (N + kBlock - 1) / kBlock * kBlock;
-    for (uint32_t s = N + lane; s < end; s += 64) {
-#pragma unroll
-      for (int i = 0; i < Q; ++i)
-        *(gptr<T>)(base + offset9<T>(s) + (uint64_t)(i * kLane * sizeof(T))) =
-            lds[i][frame * RX + frame];
-    }
-  }
   // each thread stores what it has just written
 #pragma unroll
   for (int u = 0; u < UNITS; ++u) {
     const int at = u * THREADS + (int)threadIdx.x;
     const int lx = at % RX, ly = at / RX, x = x0 + lx, y = y0 + ly;
+    // The places that pad the last tile of kBlock sites hold site 0's new
+    // populations after a single step (its lanes past the box repeat that site).
+    // A checkpoint copies them too, so the wavefront of site 0 writes them (100^2
+    // FP64, five steps a launch: 1.64 us a step without, 1.66 with; 1.73 where
+    // every wavefront of the workgroup wrote them after the other stores).
+    if (u == 0 && __builtin_expect(x0 == -frame && y0 == -frame && nx * ny % kBlock != 0, 0)) {
+      const int at0 = frame * RX + frame;
+      static_assert(THREADS >= 256, "site 0 lies in the first unit");
+      if (__any(lx == frame && ly == frame)) {
+        const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        const uint32_t N = nx * ny, end = (N + kBlock - 1) / kBlock * kBlock;
+        for (uint32_t s = N + lane; s < end; s += 64) {
+#pragma unroll
+          for (int i = 0; i < Q; ++i)
+            *(gptr<T>)(base + offset9<T>(s) + (uint64_t)(i * kLane * sizeof(T))) = lds[i][at0];
+        }
+      }
+    }
     if (lx >= frame && lx < RX - frame && ly >= frame && ly < RY - frame && x < (int)nx &&
         y < (int)ny) {
       const uint32_t s = (uint32_t)y * nx + (uint32_t)x;
