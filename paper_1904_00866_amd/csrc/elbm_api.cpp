@@ -305,67 +305,115 @@ int64_t fused_tiles(const elbm_sim* s, const Fusion& f) {
   return ((s->cfg.nx + ix - 1) / ix) * ((s->cfg.ny + iy - 1) / iy);
 }
 
-// The fusion of boxes beyond the small ones, by what bounds a single step of
-// the type there: the line between its FP64 arithmetic and its memory traffic
-// (us per step single / fused, 1001 x 601, 1024^2, 2048^2, 4096^2 unless
-// noted; fusing costs the frames' arithmetic).
-Fusion large_fusion(const elbm_config& c, int64_t sites) {
-  const bool bgk = c.alpha_mode == ELBM_ALPHA_BGK;
-  const Fusion no, two16{2, kFused16x16}, two32{2, kFused32x32}, three32{3, kFused32x32},
+// A fusion, and the most sites that its regions may compute per site of the
+// boxes: frames overlap (square boxes: 1.1 to 1.35) and a region wider than
+// what is left of a thin box computes the rest for nothing.
+struct Choice {
+  Fusion f;
+  double cover = 0.0;
+};
+
+// The fusions to consider, in order, for boxes beyond the small ones, by what
+// bounds a single step of the type there: the line between its FP64 arithmetic
+// and its memory traffic.  us per step single / fused: on 1001 x 601, 1024^2,
+// 2048^2, 4096^2 unless noted, then on thin boxes, by the cover, which place the
+// limit on it (both sides from the same state of one flow).
+struct Choices {
+  Choice c[2];
+};
+Choices large_fusions(const elbm_config& c, int64_t sites) {
+  const bool bgk = c.alpha_mode == ELBM_ALPHA_BGK, fp32 = c.alpha_fp64 == ELBM_ARITH_FP32,
+             mixed = c.alpha_fp64 == ELBM_ARITH_MIXED;
+  const Fusion two16{2, kFused16x16}, two32{2, kFused32x32}, three32{3, kFused32x32},
       two64{2, kFused64x16};
-  constexpr int64_t k400 = 400000, M = 1 << 20;
+  constexpr int64_t M = 1 << 20, k400 = 400000;
+  // mixed arithmetic on 16 x 16 regions, whose thin boxes gain up to 300,000 sites
+  // (64 x 4096, cover 1.43, FP16 4.4/4.1, FP32 deviations 5.4/5.1) and lose beyond
+  // (128 x 3000 FP16 5.4/5.6, FP32 7.0/7.2; 64 x 65536 58.6/61; 1.7: 6.1/6.9)
+  const Choice mixed16{two16, sites < 300000 ? 1.5 : 1.4};
   switch (c.storage) {
-    case ELBM_STORE_F64:  // memory-bound: LBGK 17.8/7.3 29.7/10.2 106/45 416/171,
-      // closed form 18.3/11.8 29.4/19.5 104/82 408/321
-      return bgk ? three32 : two16;
+    case ELBM_STORE_F64:  // memory-bound
+      // LBGK 17.8/7.3 29.7/10.2 106/45 416/171; 2.3: 30.6/17.2, 4.6: 43/34, 9.1: 11/17
+      if (bgk) return {{{three32, 5.0}}};
+      // closed form 18.3/11.8 29.4/19.5 104/82 408/321; 1.43: 17.1/11.8 103/87, 1.7:
+      // 32 x 8192 8.9/9.5, 32 x 32768 29.7/30.7, 32768 x 32 30.4/26.6, 2.3: 50/50, 5.1/5.4
+      return {{{two16, sites < k400 ? 1.6 : 1.75}}};
     case ELBM_STORE_F32:
-      // LBGK 9.8/6.2 14.6/8.5 57/30 214/117
-      if (bgk) return three32;
-      // FP32 arithmetic (at most two: three gains nothing) 10.2/7.8 15.0/11.4 57/39 214/151
-      if (c.alpha_fp64 == ELBM_ARITH_FP32) return two32;
-      // mixed: 512^2 5.8/5.3 on 16 x 16; 10.7/9.7 16.3/13.9 58/49 210/187 on 64 x 16
-      if (c.alpha_fp64 == ELBM_ARITH_MIXED) return sites < k400 ? two16 : two64;
-      // FP64 arithmetic: 512^2 none, 10.8/10.5 18.0/15.5 61/57 221/221
-      return sites > 3 * M / 4 && sites < 8 * M ? two32 : no;
     case ELBM_STORE_F32_DEV:
-      // mixed as for F32; FP64 arithmetic 11.3/12.1 19.3/19.1 65/71 239/272: none
-      if (c.alpha_fp64 == ELBM_ARITH_MIXED) return sites < k400 ? two16 : two64;
-      return bgk ? three32 : no;
+      // LBGK 9.8/6.2 14.6/8.5 57/30 214/117; 1.7: 7.8/6.4 57/37, 2.3: 32 x 8192 4.4/4.9,
+      // 32 x 32768 14.7/13.3, 16 x 100000 24/18, 4.6: 24/33
+      if (bgk) return {{{three32, sites < k400 ? 2.0 : 2.3}}};
+      // mixed 10.7/9.5 18.0/14.7 on 16 x 16 (on 64 x 16 10.2, 15.0; 724^2 9.7/8.5, 10.0),
+      // 1300^2 30.8/22.0, 21.5; 58/49 210/187 on 64 x 16; 1.3: 9.9/10.3, 1.55: 17.2/20.3
+      if (mixed) return {{sites < 5 * M / 4 ? mixed16 : Choice{two64, 1.28}}};
+      // Deviation storage: FP64 arithmetic 11.3/12.1 19.3/19.1 65/71 239/272, none
+      if (c.storage == ELBM_STORE_F32_DEV) return {};
+      // FP32 arithmetic (at most two: three gains nothing) 10.7/8.0 17.0/11.4 57/39
+      // 213/151, below 400,000 sites on 16 x 16 (512^2 5.2/4.7, on 32 x 32 5.4); 1.6:
+      // 8.3/9.3, and on 16 x 16 1.7: 15.2/14.5, 2.3: 27/27
+      if (fp32) {
+        if (sites < k400) return {{{two16, 1.4}}};
+        return {{{two32, 1.3}, {two16, 1.75}}};
+      }
+      // FP64 arithmetic: 512^2 none, 10.8/10.5 18.0/15.5 61/57 221/221; 1.6: 59/82, 2.1:
+      // 22/39
+      if (sites > 3 * M / 4 && sites < 8 * M) return {{{two32, 1.25}}};
+      return {};
     default:
-      // FP16: LBGK 7.2/6.5 9.7/9.8 39/33 138/129; mixed 512^2 4.7/4.1, 9.7/10.2
-      // (1024^2) 37/32 120/119; FP64 arithmetic 9.0/8.9 12.3/13.4 46/46 169/179: none
-      if (bgk) return sites > 2 * M ? two32 : no;
-      if (c.alpha_fp64 != ELBM_ARITH_MIXED) return no;
-      return sites < k400 ? two16 : sites > 2 * M && sites < 12 * M ? two64 : no;
+      // FP16: LBGK 7.2/6.5 9.7/9.8 39/33 138/129; 1.6: 37/46.  Mixed 512^2 4.7/4.1, 9.7/10.2
+      // (1024^2) 37/32 120/119; on 64 x 16 1.4: 9.7/11.8, 2.3: 35/59.  FP64 arithmetic
+      // 9.0/8.9 12.3/13.4 46/46 169/179: none
+      if (bgk) return sites > 2 * M ? Choices{{{two32, 1.25}}} : Choices{};
+      if (!mixed) return {};
+      if (sites < k400) return {{mixed16}};
+      return sites > 2 * M && sites < 12 * M ? Choices{{{two64, 1.25}}} : Choices{};
   }
 }
 
-// The fusion of launches over n simulations that may take up to `free` steps
-// without recording.  Small boxes (16 x 16 regions): as many steps as leave
+// The fusion of launches over n simulations.  Small boxes (16 x 16 regions): as many steps as leave
 // one workgroup per CU, up to six, since a launch then costs its latency only
 // (100^2 FP32, us per step: single 4.9, five steps on 169 workgroups 1.7, six on
 // 289 2.3); three where that is at most four rounds of workgroups (256^2 3.9 /
-// 2.8, 360^2 4.8 / 3.7, 512^2 6.0 / 6.2).
-Fusion fusion_of(elbm_sim* const* sims, size_t n, int64_t free) {
+// 2.8, 360^2 4.8 / 3.7, 512^2 6.0 / 6.2).  A thin box has as many rounds with far
+// fewer sites, so that its single steps stay short: the closed form in FP64
+// arithmetic takes three steps up to three rounds then (2 x 6000, two rounds,
+// 3.6 / 2.5, 1 x 12000, four, 3.7 / 3.8; the others 3.3 / 3.3 and better at four).
+Fusion fusion_of(elbm_sim* const* sims, size_t n) {
   Fusion f;
-  if (free < 2 || !sims[0]->fused) return f;
+  if (!sims[0]->fused) return f;
   int64_t sites = 0;
   for (size_t k = 0; k < n; ++k) {  // 32-bit byte offsets into a buffer
     if (elbm_checkpoint_bytes(sims[k]) > UINT32_MAX) return f;
     sites += sims[k]->L.N;
   }
-  constexpr int kMost = 6, kCUs = 256, kRounds = 4;
-  const auto tiles = [&](int nsub) {
+  const auto tiles = [&](const Fusion& g) {
     int64_t t = 0;
-    for (size_t k = 0; k < n; ++k) t += fused_tiles(sims[k], Fusion{nsub, kFused16x16});
+    for (size_t k = 0; k < n; ++k) t += fused_tiles(sims[k], g);
     return t;
   };
-  if (tiles(3) <= kRounds * kCUs) {
+  const auto cover = [&](const Fusion& g) {
+    return double(tiles(g)) * (kFusedX[g.geom] * kFusedY[g.geom]) / double(sites);
+  };
+  constexpr int kMost = 6, kCUs = 256;
+  const elbm_config& c = sims[0]->cfg;
+  const Fusion three16{3, kFused16x16};
+  const bool fp64 = c.alpha_mode == ELBM_ALPHA_CLOSED && c.alpha_fp64 == ELBM_ARITH_FP64;
+  const int64_t rounds = fp64 && cover(three16) > 3.0 ? 3 : 4;
+  if (tiles(three16) <= rounds * kCUs) {
     f.nsub = kMost;
-    while (f.nsub > 3 && tiles(f.nsub) > kCUs) --f.nsub;
+    while (f.nsub > 3 && tiles(f) > kCUs) --f.nsub;
   } else {
-    f = large_fusion(sims[0]->cfg, sites);
+    for (const Choice& g : large_fusions(c, sites).c)
+      if (g.f.nsub > 1 && cover(g.f) <= g.cover) {
+        f = g.f;
+        break;
+      }
   }
+  return f;
+}
+
+// f with as many steps as fit into `free`, the steps that need not record.
+Fusion fit(Fusion f, int64_t free) {
   while (f.nsub > 1 && f.steps() > free) --f.nsub;
   if (f.nsub == 1) f.geom = kFused16x16;
   return f;
@@ -429,11 +477,12 @@ template <class Launch>
 hipError_t advance(elbm_sim* const* sims, const char* ends, size_t n, int64_t steps,
                    const Launch& launch) {
   char last[kMaxBatch];
+  const Fusion most = steps > 1 ? fusion_of(sims, n) : Fusion{};
   for (int64_t left = steps; left > 0;) {
     int64_t free = left;
     for (size_t k = 0; k < n; ++k)
       if (ends[k]) free = std::min(free, free_steps(sims[k], left));
-    const Fusion f = fusion_of(sims, n, free);
+    const Fusion f = fit(most, free);
     for (size_t k = 0; k < n; ++k) last[k] = ends[k] && left == f.steps();
     const hipError_t e = launch(sims, last, n, f);
     if (e != hipSuccess) return e;

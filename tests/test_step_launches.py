@@ -47,6 +47,51 @@ def test_groups_of_sixteen_choose_for_themselves(n, kw):
     assert launches([(n, n)] * 40, [60] * 40, **kw) == 2 * one + rest
 
 
+THIN = [((1, 100000), dict(storage="f64")), ((2, 500000), dict(storage="f64")),
+        ((4, 100000), dict(storage="f64")), ((16, 8000), dict(storage="f64")),
+        ((32, 8192), dict(storage="f64")), ((1, 100000), dict(storage="f64", mode="bgk")),
+        ((2, 500000), dict(mode="bgk")), ((8, 200000), dict(mode="bgk")),
+        ((32, 8192), dict(mode="bgk")), ((8, 200000), dict(fp64="fp32")),
+        ((1, 100000), dict(fp64="mixed")), ((2, 500000), dict(fp64="mixed")),
+        ((16, 100000), dict(fp64="mixed")), ((32, 32768), dict(fp64="mixed")),
+        ((128, 3000), dict(fp64="mixed")), ((2, 500000), dict()), ((32, 32768), dict()),
+        ((32768, 32), dict()), ((64, 65536), dict()), ((64, 65536), dict(fp64="mixed")),
+        ((1, 12000), dict()), ((4, 11000), dict()),
+        ((64, 65536), dict(storage="f16dev", mode="bgk")),
+        ((64, 65536), dict(storage="f16dev", fp64="mixed")),
+        ((1, 100000), dict(storage="f16dev", fp64="mixed")),
+        ((2, 500000), dict(storage="f32dev", fp64="mixed"))]
+
+
+@pytest.mark.parametrize("box,kw", THIN)
+def test_thin_boxes_take_single_steps(box, kw):
+    """Boxes of which a region holds little more than a few sites: fused, its other
+    sites would be computed for nothing (up to 15 times the time of single steps)."""
+    assert launches([box], [60], **dict(dict(storage="f32"), **kw)) == 60
+
+
+SQUARE = [((1001, 601), 20, dict(storage="f64", mode="bgk")),
+          ((2048, 2048), 30, dict(storage="f64")), ((4096, 4096), 30, dict(storage="f64")),
+          ((1024, 1024), 20, dict(mode="bgk")), ((1001, 601), 30, dict(fp64="fp32")),
+          ((640, 640), 30, dict(fp64="mixed")), ((4096, 4096), 30, dict(fp64="mixed")),
+          ((365, 365), 20, dict(fp64="mixed")), ((512, 512), 30, dict(fp64="mixed")),
+          ((901, 901), 30, dict()), ((2048, 2048), 30, dict()), ((1001, 601), 60, dict()),
+          ((4096, 4096), 60, dict()), ((2048, 2048), 30, dict(storage="f16dev", mode="bgk")),
+          ((1450, 1447), 30, dict(storage="f16dev", fp64="mixed")),
+          ((620, 620), 30, dict(storage="f16dev", fp64="mixed")),
+          ((64, 8192), 20, dict(storage="f64", mode="bgk")),
+          ((64, 65536), 30, dict(storage="f64")),
+          ((64, 4096), 30, dict(storage="f16dev", fp64="mixed")), ((2, 6000), 20, dict()),
+          ((1, 2000), 12, dict()), ((8, 9000), 20, dict())]
+
+
+@pytest.mark.parametrize("box,want,kw", SQUARE)
+def test_other_boxes_fuse(box, want, kw):
+    """Near-square boxes on either side of each type's lines, and thin ones where
+    the regions are worth it."""
+    assert launches([box], [60], **dict(dict(storage="f32"), **kw)) == want
+
+
 def test_invalid_batches():
     cfg = elbm.make_config("d2q9", 64, 64)
     with pytest.raises(elbm.ElbmError, match="nsteps < 0"):
