@@ -251,19 +251,30 @@ struct Site {
     return h;
   }
 
-  // One pass f(i, 1/W_i, x_i, f^eq_i, g_i) over the directions for the rare
-  // tier, the root solvers' log1p passes and the collision that follows
-  // them.  Up to nine directions: on the registers' populations, three
-  // directions at a time (the fences bound what the scheduler interleaves,
-  // and with it the registers held; three independent logarithm chains hide
-  // most of each other's latency).  With 27 directions the populations are
-  // not kept through the logarithms (registers): a loop over the rows
-  // (c_y, c_z) re-reads the three of each, together, from the caches this
-  // wavefront has just filled.  So do the root solvers' passes on any lattice
-  // (REREAD), one direction at a time: their four unrolled tiles hold one
-  // body of the logarithms each, more would keep the tiles from unrolling.
+  // One pass over the directions for the rare tier, the root solvers' log1p
+  // passes (sweep: f(x_i, f^eq_i)) and the collision that follows the rare tier
+  // (sweep_collision: f(i, 1/W_i, f^eq_i, g_i)).  Up to nine directions: on the
+  // registers' populations, three directions at a time (the fences bound what
+  // the scheduler interleaves, and with it the registers held; three
+  // independent logarithm chains hide most of each other's latency).  With 27
+  // directions the populations are not kept through the logarithms (registers):
+  // a loop over the rows (c_y, c_z) re-reads the three of each, together, from
+  // the caches this wavefront has just filled.  So do the root solvers' passes
+  // on any lattice (REREAD), one direction at a time: their four unrolled tiles
+  // hold one body of the logarithms each, more would keep the tiles from
+  // unrolling.
   template <bool REREAD = kReread, class F>
   __device__ __forceinline__ void sweep(const F& f) const {
+    each<REREAD>([&](int, auto, R xi, R fi, R) { f(xi, fi); });
+  }
+  template <class F>
+  __device__ __forceinline__ void sweep_collision(const F& f) const {
+    each<kReread>([&](int i, R invW, R, R fi, R gi) { f(i, invW, fi, gi); });
+  }
+  struct NotFormed {};  // in the place of 1/W_i where a pass does not form it
+  // f(i, 1/W_i, x_i, f^eq_i, g_i) for each direction
+  template <bool REREAD, class F>
+  __device__ __forceinline__ void each(const F& f) const {
     if constexpr (D == 3) {
       const Where w = locate<D>(*desc, site);
 #pragma unroll 1
@@ -300,8 +311,7 @@ struct Site {
           return dx == 0 ? q0 : (dx == 1 ? q1 : q2);
         };
         const R gi = Codec<S, R>::dec(gv, W, rho_ref);
-        // (no collision is swept this way: 1/W_i is not formed)
-        f(i, R(0), fma(gi, pick(r01), R(-1)), pick(f01), gi);
+        f(i, NotFormed{}, fma(gi, pick(r01), R(-1)), pick(f01), gi);
       }
     } else {
       const Pass p = pass_opaque();
@@ -549,7 +559,7 @@ struct SiteDevT {
           const int i0 = dx, i1 = dx + 3, i2 = dx + 12;  // as in Site::sweep
           const A iW = z == 2 ? A(L::invW(i0)) : z == 1 ? A(L::invW(i1)) : A(L::invW(i2));
           A si = A(gv[dx]);
-        if constexpr (!S::dev) si = fma(si, iW, -r);
+          if constexpr (!S::dev) si = fma(si, iW, -r);
           f(dx + 3 * n, si, fma(sel3(seqB[dx], dy), dl, sel3(seqA[dx], dy)),
             z == 2 ? L::W(i0) : z == 1 ? L::W(i1) : L::W(i2));
           __builtin_amdgcn_sched_barrier(0);
@@ -572,9 +582,7 @@ struct SiteDevT {
   }
   template <bool REREAD = kReread, class F>
   __device__ __forceinline__ void sweep(const F& f) const {
-    sweep_dev<REREAD>([&](int i, A si, A seqi, double W) {
-      f(i, 0.0, x_far(si, seqi), fe_far(seqi, W), 0.0);
-    });
+    sweep_dev<REREAD>([&](int, A si, A seqi, double W) { f(x_far(si, seqi), fe_far(seqi, W)); });
   }
 };
 template <int D, class S>
@@ -584,7 +592,7 @@ using SiteDev = SiteDevT<D, S, float>;
 template <class V, class R>
 __device__ __forceinline__ R S_log(const V& v, R a) {
   R s = R(0);
-  v.template sweep<true>([&](int, R, R xi, R fi, R) { s += fi * phi_log<R>((R(1) - a) * xi); });
+  v.template sweep<true>([&](R xi, R fi) { s += fi * phi_log<R>((R(1) - a) * xi); });
   return s;
 }
 
@@ -595,7 +603,7 @@ __device__ __forceinline__ void S_dS_log(const V& v, R a, R& Sv, R& dS, R* sA = 
   Sv = R(0);
   dS = R(0);
   R sa = R(0);
-  v.template sweep<true>([&](int, R, R xi, R fi, R) {
+  v.template sweep<true>([&](R xi, R fi) {
     const R y = (R(1) - a) * xi;
     const R l = dlog_clamped<R>(y);
     Sv += fi * ((y <= R(-1)) ? R(1) : (R(1) + y) * l - y);
@@ -737,7 +745,7 @@ template <bool REREAD, class V, class R>
 __device__ __forceinline__ void far_sums(const V& v, R& xabs, R& xmax, R& E, R& O) {
   R sE = R(0), sO = R(0), xa = R(0), xm = R(-1);
   const SeriesK<R, Base<R>::KL> ser;
-  v.template sweep<REREAD>([&](int, R, R xi, R fi, R) {
+  v.template sweep<REREAD>([&](R xi, R fi) {
     xa = fmax(xa, fabs(xi));
     xm = fmax(xm, xi);
     ser.accum(xi, fi, sE, sO);
@@ -752,7 +760,7 @@ __device__ __forceinline__ void far_sums(const V& v, R& xabs, R& xmax, R& E, R& 
 template <bool REREAD, class V, class R>
 __device__ __forceinline__ void log_sums(const V& v, R astar, R& Dv, R& Ds, R& Gs) {
   R sD = R(0), sS = R(0), sG = R(0);
-  v.template sweep<REREAD>([&](int, R, R xi, R fi, R) {
+  v.template sweep<REREAD>([&](R xi, R fi) {
     const R px = phi_log<R>(xi);
     const R py = phi_log<R>((R(1) - astar) * xi);
     sD += fi * px;
@@ -1796,7 +1804,6 @@ __device__ __forceinline__ SiteOut site_update_fp(const SimDesc& d,
                                                Acc& acc, int diag) {
   using L = Lattice<D>;
   constexpr int Q = L::Q;
-  using T = typename S::T;
   const uint32_t sl = live ? s : 0u;  // the site whose values were loaded
 
   Site<D, S, R> v;
@@ -1956,7 +1963,7 @@ __device__ __forceinline__ uint32_t site_update_rare_fp(const SimDesc& d, const 
   const gaddr blk = block_base<Q>(dst, s);
   const R ab = ao.alpha * (R)d.beta;
   R ftmin = R(INFINITY);
-  v.sweep([&](int i, R invW, R, R fi, R gi) {
+  v.sweep_collision([&](int i, R invW, R fi, R gi) {
     const R ft = fma(ab, fi - gi, gi);
     ftmin = fmin(ftmin, ft);
     st_nt<T>(blk + (uint64_t)i * kLane * es, kLane * es, lo, Codec<S, R>::enc(ft, invW, v.rho_ref));

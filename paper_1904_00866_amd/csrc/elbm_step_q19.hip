@@ -171,9 +171,9 @@ struct SiteQ19 {
     return h;
   }
 
-  // One pass f(i, 1/W_i, x_i, f^eq_i, g_i) for the rare tier, the root
-  // solvers' log1p passes and the collision (see Site::sweep): one direction
-  // at a time, re-read from the caches.  Rows of three together, as with 27
+  // One pass for the rare tier and the root solvers' log1p passes (sweep), or
+  // the collision (sweep_collision; see Site): one direction at a time,
+  // re-read from the caches.  Rows of three together, as with 27
   // directions, spill twice as many registers (the nine rows are not alike,
   // so the body exists twice) and cost the Newton mode 12 %.
   __device__ __forceinline__ static R sel9(const R (&a)[3][3], int dx, int dy) {
@@ -184,6 +184,14 @@ struct SiteQ19 {
   }
   template <bool REREAD = true, class F>
   __device__ __forceinline__ void sweep(const F& f) const {
+    each([&](int, R, R xi, R fi, R) { f(xi, fi); });
+  }
+  template <class F>
+  __device__ __forceinline__ void sweep_collision(const F& f) const {
+    each([&](int i, R invW, R, R fi, R gi) { f(i, invW, fi, gi); });
+  }
+  template <class F>
+  __device__ __forceinline__ void each(const F& f) const {
     const Where w = locate<3>(*desc, site);
 #pragma unroll 1
     for (int i = 0; i < Q; ++i) {
@@ -405,7 +413,7 @@ __device__ __forceinline__ uint32_t update_rare_q19(const SimDesc& d,
   R ftmin = R(INFINITY);
   const uint32_t lo = (s & 63u) * es;
   const gaddr blk = block_base<Q>(dst, s);
-  v.sweep([&](int i, R invW, R, R fi, R gi) {
+  v.sweep_collision([&](int i, R invW, R fi, R gi) {
     const R ft = fma(ab, fi - gi, gi);
     ftmin = fmin(ftmin, ft);
     st_nt<T>(blk + (uint64_t)i * kLane * es, kLane * es, lo, Codec<S, R>::enc(ft, invW, v.rho_ref));
