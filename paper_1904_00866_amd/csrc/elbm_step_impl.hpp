@@ -2021,13 +2021,19 @@ __device__ __forceinline__ uint32_t site_update_rare(const SimDesc& d,
 // VGPRs: the decoded deviations and the per-axis factors of both the
 // equilibrium and its reciprocal; four waves spill in the common path and
 // run 5.02 ms against 3.86 ms at 512^3 with mixed arithmetic).
+// Newton on D3Q27 with FP32 deviations: two, since with its power sums three
+// spill 45 registers, most of them in the path of every site (128^3, us a
+// step near equilibrium: one series pass per iteration 234, power sums at three
+// waves 332, at two 161; in turbulence 514, 510, 441).  FP32 spills 21 and FP16
+// 31, elsewhere: 152 and 175 at three waves.
 // Mixed arithmetic on 2-byte storage, up to nine directions: six, which its
 // common path fits (78 VGPRs); five cost 2.5 % at 4096^2.
-template <class S, int MODE, class AP = double, int Q = 27, bool SUMS = true>
+template <class S, int MODE, class AP, int Q, bool SUMS>
 constexpr int step_waves() {
   if (sizeof(typename S::T) == 2 && MODE == kClosed && kIsMixed<AP> && Q <= 9 && !SUMS) return 6;
   if (sizeof(typename S::T) == 2 && MODE == kClosed) return 3;
   if (sizeof(typename S::T) <= 4 && (MODE == kClosed || MODE == kBGK)) return ELBM_CLOSED_WAVES;
+  if (std::is_same<S, StoreF32Dev>::value && MODE == kNewton && Q == 27) return 2;
   if (sizeof(typename S::T) <= 4 && (MODE == kNewton || MODE == kSecant || MODE == kBisect))
     return ELBM_NEWTON_WAVES;
   return 1;

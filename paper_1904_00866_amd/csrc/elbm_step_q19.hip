@@ -423,7 +423,8 @@ __device__ __forceinline__ uint32_t update_rare_q19(const SimDesc& d,
 
 // The step kernel: the workgroup, tile and XCD-aware order of k_step.
 template <class S, int MODE, class R, bool SUMS>
-__global__ void __launch_bounds__(kBlock, (step_waves<S, MODE>())) k_step_q19(const BatchArgs args) {
+__global__ void __launch_bounds__(kBlock, (step_waves<S, MODE, R, 19, SUMS>()))
+k_step_q19(const BatchArgs args) {
   using T = typename S::T;
   constexpr int Q = 19;
   constexpr int ELBM_TILES = tiles_per_block(sizeof(T), Q);

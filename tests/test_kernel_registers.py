@@ -1,0 +1,48 @@
+"""Registers that the compiler spilled in kernels whose path of every site is
+sensitive to it, from the metadata of the library built here (nothing runs)."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_1904_00866_amd import build as B
+
+
+@pytest.fixture(scope="module")
+def spills(tmp_path_factory):
+    """Mangled kernel name -> spilled vector registers, of every code object in the
+    library."""
+    readelf = os.path.join(os.path.dirname(B.hipcc()), "..", "llvm", "bin", "llvm-readelf")
+    lib = open(B.LIB, "rb").read()
+    part = tmp_path_factory.mktemp("objects") / "part.co"
+    out = {}
+    for m in re.finditer(rb"\x7fELF\x02\x01\x01", lib):
+        at = m.start()
+        machine, = struct.unpack_from("<H", lib, at + 18)
+        if machine != 224:  # EM_AMDGPU
+            continue
+        shoff, = struct.unpack_from("<Q", lib, at + 40)
+        shentsize, shnum = struct.unpack_from("<HH", lib, at + 58)
+        part.write_bytes(lib[at:at + shoff + shentsize * shnum])
+        text = subprocess.run([readelf, "--notes", str(part)], capture_output=True, text=True,
+                              check=True).stdout
+        for k in re.split(r"\n  - \.", text)[1:]:
+            name = re.search(r"\.name:\s+(_Z\S+)", k)
+            count = re.search(r"\.vgpr_spill_count:\s+(\d+)", k)
+            if name and count:
+                out[name.group(1)] = int(count.group(1))
+    return out
+
+
+def _worst(spills, kernel):
+    found = [v for k, v in spills.items() if re.search(kernel, k)]
+    assert found, kernel
+    return max(found)
+
+
+def test_newton_d3q27_fp32_deviations(spills):
+    """Two waves per SIMD and no spills (45 at three cost 40 % of its time near
+    equilibrium)."""
+    assert _worst(spills, r"6k_stepILi3ENS_11StoreF32DevELi1EdLb0") == 0
