@@ -46,3 +46,9 @@ def test_newton_d3q27_fp32_deviations(spills):
     """Two waves per SIMD and no spills (45 at three cost 40 % of its time near
     equilibrium)."""
     assert _worst(spills, r"6k_stepILi3ENS_11StoreF32DevELi1EdLb0") == 0
+
+
+def test_secant_d3q19_deviations(spills):
+    """24 spilled with the rare tier in line, in the path of every site, cost 15 to
+    30 %."""
+    assert _worst(spills, r"k_step_q19INS_11Store(F32|F16)DevELi4EdLb0") <= 16
