@@ -372,9 +372,9 @@ Choices large_fusions(const elbm_config& c, int64_t sites) {
 
 // The fusion of launches over n simulations.  Small boxes (16 x 16 regions): as many steps as leave
 // one workgroup per CU, up to six, since a launch then costs its latency only
-// (100^2 FP32, us per step: single 4.9, five steps on 169 workgroups 1.7, six on
-// 289 2.3); three where that is at most four rounds of workgroups (256^2 3.9 /
-// 2.8, 360^2 4.8 / 3.7, 512^2 6.0 / 6.2).  A thin box has as many rounds with far
+// (100^2 FP32, us per step: single 3.4, five steps on 169 workgroups 1.55, six on
+// 289 1.95); three where that is at most four rounds of workgroups (360^2 4.4 /
+// 3.8, 512^2 5.8 / 6.5).  A thin box has as many rounds with far
 // fewer sites, so that its single steps stay short: the closed form in FP64
 // arithmetic takes three steps up to three rounds then (2 x 6000, two rounds,
 // 3.6 / 2.5, 1 x 12000, four, 3.7 / 3.8; the others 3.3 / 3.3 and better at four).

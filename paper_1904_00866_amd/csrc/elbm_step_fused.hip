@@ -11,12 +11,13 @@
 //
 // What it buys: a small box, whose step is a launch and the latency of one
 // site's arithmetic, pays one launch for nsub steps (64^2 in FP32, six steps:
-// 4.6 -> 1.6 us a step), and a large one moves its state once per nsub steps:
-// LBGK becomes two times faster (FP64 4096^2, three steps: 416 -> 171 us a
-// step), FP64 closed form 408 -> 321.  The FP32 closed form is bound by its
-// FP64 arithmetic then: per step as many vector instructions as single steps
-// (13.6M at 1500^2; the frame's sites cost what the pull from LDS saves), 24 us
-// of issue in 29.5 us a step (single steps 35.7).
+// 3.3 -> 1.4 us a step), and a large one moves its state once per nsub steps:
+// LBGK becomes two times faster (FP64 4096^2, three steps: 416 -> 172 us a
+// step), FP64 closed form 405 -> 325.  The FP32 closed form is bound by its
+// FP64 arithmetic then: 14.2M vector instructions a step at 1500^2, of single
+// steps 13.7M (the frame's sites cost what the pull from LDS saves), about 25
+// us of issue in 34 us a step (single steps 38).  A box whose tiles are mostly
+// frame computes far more (fusion_of() has the limits).
 // It records no diagnostics (those belong to the last step of a call, which is
 // launched singly when it records).
 #include "elbm_step_impl.hpp"
